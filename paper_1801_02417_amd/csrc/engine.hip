@@ -448,10 +448,10 @@ T* Engine<R>::dalloc(size_t count) {
 }
 
 template <typename R>
-void Engine<R>::dfree(void* p) {
+void Engine<R>::dfree(const void* p) {
   if (!p) return;
   auto it = std::find(allocs_.begin(), allocs_.end(), p);
-  if (it != allocs_.end()) { allocs_.erase(it); (void)hipFree(p); }
+  if (it != allocs_.end()) { (void)hipFree(*it); allocs_.erase(it); }
 }
 
 template <typename R>
@@ -503,9 +503,9 @@ static std::vector<int4> xcd_contiguous(const std::vector<int4>& v) {
 template <typename R>
 void Engine<R>::upload_chunks() {
   const Geometry& g = geo_;
-  dfree((void*)h_.run_pack);
-  dfree((void*)h_.chunk_ent); dfree((void*)h_.tile_slots); dfree((void*)h_.chunks); dfree((void*)h_.slot_box);
-  dfree((void*)h_.tile_box); dfree((void*)h_.small_ids); dfree(h_.gpart);
+  dfree(h_.run_pack);
+  dfree(h_.chunk_ent); dfree(h_.tile_slots); dfree(h_.chunks); dfree(h_.slot_box);
+  dfree(h_.tile_box); dfree(h_.small_ids); dfree(h_.gpart);
   h_.run_pack = upload<int>(g.run_pack.data(), std::max<size_t>(1, g.run_pack.size()));
   h_.chunk_ent = upload<int2>(g.chunk_ent.data(), std::max<size_t>(1, g.chunk_ent.size()));
   h_.tile_slots = upload<int2>(g.tile_slots.data(), std::max<size_t>(1, g.tile_slots.size()));
@@ -653,7 +653,7 @@ bool Engine<R>::set_data_dev(const double* Y_dev, double eps) {
 
 template <typename R>
 void Engine<R>::set_mixing(const double* mix_sorted) {
-  dfree((void*)h_.mix);
+  dfree(h_.mix);
   h_.mix = nullptr;
   if (mix_sorted) h_.mix = upload_conv(mix_sorted, (size_t)geo_.M * 32);
   desc_dirty_ = true;
@@ -696,7 +696,7 @@ void Engine<R>::set_prior(uint32_t mask, int levels, const double* weights, doub
   // release a previous prior
   for (int c = 0; c < NUM_COEF; ++c) { dfree(h_.coef[c]); h_.coef[c] = nullptr; }
   dfree(h_.ll); h_.ll = nullptr;
-  dfree((void*)h_.filters); h_.filters = nullptr;
+  dfree(h_.filters); h_.filters = nullptr;
   items_.dirac.clear(); items_.synfinal.clear(); items_.synsplit.clear(); items_.coarse.clear();
   for (int l = 0; l <= kMaxLevels; ++l) {
     items_.ana[l].clear(); items_.syn[l].clear(); items_.ana_d[l].clear(); items_.syn_d[l].clear();

@@ -186,7 +186,7 @@ struct Engine {
   template <typename T> T* dalloc(size_t count);
   template <typename T> T* upload(const T* host, size_t count);
   R* upload_conv(const double* host, size_t count);
-  void dfree(void* p);
+  void dfree(const void* p);
   void zero(void* p, size_t bytes);
   void realloc_partials();
   void upload_items();
