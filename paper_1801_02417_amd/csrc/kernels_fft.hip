@@ -15,10 +15,17 @@
 // cells.  The grid is stored transposed ([k2][k1]); the de-gridding and gridding kernels
 // index it that way.  Every cell carries the four Stokes channels, which share twiddles.
 //
-// Line FFTs run in LDS as Stockham autosort passes (radix 8, then 4 or 2) with the data of
-// each butterfly held in registers across a barrier, so a single LDS buffer suffices.  Each
-// thread owns one Stokes channel of 8 cells per pass (one radix-8, two radix-4 or four
-// radix-2 butterflies).
+// Line FFTs are Stockham autosort passes (radix 8, the last one 8, 4 or 2).  A thread owns one
+// Stokes channel of the eight cells tl + q K/8 of a line: these are the inputs of its first
+// butterfly, what it reads back after every exchange through LDS, and what the last pass leaves
+// it, so the first pass takes its inputs from memory and the last one stores its outputs with no
+// LDS in between.  The zero padding and the crop are then the register indices q = 2..5, and four
+// adjacent lanes (the channels of a cell) trade their four remaining cells so that each holds
+// all channels of one pixel (quad_transpose) for the pointwise steps.  The passes are bound by
+// the latency of their memory and LDS round trips, not by bytes; against staging the line in LDS
+// first and storing it from there (event times, less the 5 us that the events add): 512^2 image
+// P5 24 -> 13 us, P9 + P1 + P4 39 -> 23 us, P8 43 -> 34 us; 128^2 P5 3.9 -> 1.9 us, P9 + P1 + P4
+// 8.2 -> 5.0 us.
 #include "common.hpp"
 #include "launch.hpp"
 #include "primal.hpp"
@@ -62,71 +69,100 @@ __device__ inline void dft8(cplx<R>* a, bool inv) {
   a[3] = cadd(e3, o3); a[7] = csub(e3, o3);
 }
 
-// One Stockham pass of radix RAD over the lines in LDS.  A thread owns one Stokes channel
-// `ch` of 8 cells: it reads the inputs of its 8/RAD butterflies into registers and writes
-// the outputs after a barrier, so the pass is done in place.  The four lanes of a cell are
-// adjacent, so their 8-byte (16-byte in FP64) accesses are contiguous.
+// Where cell c of a line is kept in LDS: one cell in nine is left empty, which puts the radix-8
+// pass's writes (eight cells apart) on different banks.
+__device__ inline int lds_cell(int c) { return c + (c >> 3); }
+
+// The twiddles of a pass of radix RAD after Ns = K / rem points: butterfly b of the thread is
+// j = tl + b K/8.
 template <typename R, int RAD>
-__device__ inline void stockham_pass(cplx<R>* x, int K, int Ns, int tl, int per_line, int ch, bool inv,
-                                     const cplx<R>* __restrict__ tw) {
-  constexpr int NB = 8 / RAD;
-  constexpr int LR = RAD == 8 ? 3 : RAD == 4 ? 2 : 1;   // log2 RAD
-  // K and Ns are powers of two: divisions by them are shifts and masks
-  const int lk = lg2(K), ls = lg2(Ns);
-  const int stride = K >> LR;
-  cplx<R> v[8];
-  // the pass's twiddles first, so that their loads are in flight across the barrier
-  const int twstep = K >> (ls + LR);
-  cplx<R> wt[NB][RAD];
+__device__ __forceinline__ void load_twiddles(cplx<R>* wt, int lk, int ls, int tl, const cplx<R>* __restrict__ tw) {
+  constexpr int NB = 8 / RAD, LR = RAD == 8 ? 3 : RAD == 4 ? 2 : 1;
+  const int Ns = 1 << ls, step = lk - ls - LR;
 #pragma unroll
   for (int b = 0; b < NB; ++b) {
-    const int k = (tl + b * per_line) & (Ns - 1);
+    const int k = (tl + (b << (lk - 3))) & (Ns - 1);
 #pragma unroll
-    for (int r = 1; r < RAD; ++r) wt[b][r] = tw[r * k * twstep];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int b = q / RAD, r = q - b * RAD;
-    v[q] = x[4 * (tl + b * per_line + r * stride) + ch];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const int j = tl + b * per_line;
-    const int k = j & (Ns - 1);
-#pragma unroll
-    for (int r = 1; r < RAD; ++r) {
-      cplx<R> w = wt[b][r];
-      if (inv) w.im = -w.im;
-      v[b * RAD + r] = cmul(v[b * RAD + r], w);
-    }
-    if (RAD == 8) dft8(v + b * 8, inv);
-    else if (RAD == 4) dft4(v[b * 4], v[b * 4 + 1], v[b * 4 + 2], v[b * 4 + 3], inv);
-    else dft2(v[b * 2], v[b * 2 + 1]);
-    const int base = ((j >> ls) << (ls + LR)) + k;
-#pragma unroll
-    for (int r = 0; r < RAD; ++r) x[4 * (base + r * Ns) + ch] = v[b * RAD + r];
+    for (int r = 1; r < RAD; ++r) wt[b * RAD + r] = tw[(r * k) << step];
   }
 }
 
-// In-place Stockham FFT (radix 8 passes, then one radix-4 or radix-2 pass) of the lines held
-// in `lds` (line l at lds + l*K).  Called by CELLS/2 threads: thread t handles channel t % 4 of
-// the 8 cells of butterfly group t / 4, on line (t / 4) / (K/8).
-template <typename R, int CELLS>
-__device__ void fft_lines(Cell<R>* lds, int K, bool inv, const cplx<R>* __restrict__ tw) {
-  const int per_line = K >> 3;
-  const int ch = threadIdx.x & 3, grp = threadIdx.x >> 2;
-  const int l = grp >> lg2(per_line), tl = grp & (per_line - 1);
-  cplx<R>* x = (cplx<R>*)(lds + l * K);
-  int Ns = 1;
-  while (Ns < K) {
-    const int rem = K >> lg2(Ns);
-    if (rem % 8 == 0) { stockham_pass<R, 8>(x, K, Ns, tl, per_line, ch, inv, tw); Ns *= 8; }
-    else if (rem % 4 == 0) { stockham_pass<R, 4>(x, K, Ns, tl, per_line, ch, inv, tw); Ns *= 4; }
-    else { stockham_pass<R, 2>(x, K, Ns, tl, per_line, ch, inv, tw); Ns *= 2; }
+// The butterflies of one pass of radix RAD on v[q] = x[tl + q K/8]: butterfly b takes q = b + r NB.
+template <typename R, int RAD, bool INV>
+__device__ __forceinline__ void butterflies(cplx<R>* v, const cplx<R>* wt) {
+  constexpr int NB = 8 / RAD;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    cplx<R> a[RAD];
+#pragma unroll
+    for (int r = 0; r < RAD; ++r) {
+      a[r] = v[b + r * NB];
+      if (r > 0) {
+        cplx<R> w = wt[b * RAD + r];
+        if (INV) w.im = -w.im;
+        a[r] = cmul(a[r], w);
+      }
+    }
+    if constexpr (RAD == 8) dft8(a, INV);
+    else if constexpr (RAD == 4) dft4(a[0], a[1], a[2], a[3], INV);
+    else dft2(a[0], a[1]);
+#pragma unroll
+    for (int r = 0; r < RAD; ++r) v[b + r * NB] = a[r];
   }
-  __syncthreads();
+}
+
+// FFT of the line (unnormalised) whose cells tl + q K/8 of one channel the thread holds in v: in
+// natural order before and after.  x: the line's LDS cells, channel ch at x[4 lds_cell(c) + ch].
+// Called by the whole workgroup.
+template <typename R, bool INV>
+__device__ __forceinline__ void fft_line(cplx<R>* v, cplx<R>* x, int lk, int tl, int ch, const cplx<R>* __restrict__ tw) {
+  dft8(v, INV);                                    // the first pass has no twiddles
+  for (int ls = 3; ls < lk; ls += 3) {
+    // the next pass's twiddles are requested before the exchange, so that they arrive during it
+    const int rem = lk - ls;
+    cplx<R> wt[8];
+    if (rem >= 3) load_twiddles<R, 8>(wt, lk, ls, tl, tw);
+    else if (rem == 2) load_twiddles<R, 4>(wt, lk, ls, tl, tw);
+    else load_twiddles<R, 2>(wt, lk, ls, tl, tw);
+    const int pNs = 1 << (ls - 3);                 // the previous pass: radix 8 after pNs points
+    const int base = ((tl >> (ls - 3)) << ls) + (tl & (pNs - 1));
+    __syncthreads();                               // the buffer is no longer read
+#pragma unroll
+    for (int r = 0; r < 8; ++r) x[4 * lds_cell(base + (r << (ls - 3))) + ch] = v[r];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = x[4 * lds_cell(tl + (q << (lk - 3))) + ch];
+    if (rem >= 3) butterflies<R, 8, INV>(v, wt);
+    else if (rem == 2) butterflies<R, 4, INV>(v, wt);
+    else butterflies<R, 2, INV>(v, wt);
+  }
+}
+
+// The value of lane ^ 1 (X = 1) or lane ^ 2 (X = 2), by a DPP lane move.
+template <int X, typename V>
+__device__ __forceinline__ V quad_xor(V v) {
+  union { V v; int w[sizeof(V) / 4]; } a, b;
+  a.v = v;
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(V) / 4); ++k) b.w[k] = __builtin_amdgcn_mov_dpp(a.w[k], X == 1 ? 0xB1 : 0x4E, 0xf, 0xf, true);
+  return b.v;
+}
+// Transposes the 4 x 4 values of four adjacent lanes: lane j's a[i] becomes lane i's a[j].
+template <typename R>
+__device__ __forceinline__ void quad_transpose(R* a) {
+  const bool h1 = threadIdx.x & 1, h2 = threadIdx.x & 2;
+#pragma unroll
+  for (int i = 0; i < 4; i += 2) {
+    const R t = quad_xor<1>(h1 ? a[i] : a[i + 1]);
+    a[i] = h1 ? t : a[i];
+    a[i + 1] = h1 ? a[i + 1] : t;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const R t = quad_xor<2>(h2 ? a[i] : a[i + 2]);
+    a[i] = h2 ? t : a[i];
+    a[i + 2] = h2 ? a[i + 2] : t;
+  }
 }
 
 // a product that is rounded on its own (never contracted into a following add)
@@ -146,27 +182,38 @@ __device__ inline Cell<R> zero_cell() {
 
 // PASS: 0 = P4 image rows -> half, 1 = P5 half -> grid, 2 = P8 grid -> half, 3 = P9 half -> image,
 // 4 = P9, P1 and P4 of the next iteration in one pass: half -> inverse row FFT -> Re phi^dagger B
-// of the row's pixels (kept in LDS) -> primal step -> X -> forward row FFT -> half.
-// PM >= 0 (PASS 0 and 4): the primal step of mode PM runs on each pixel as the row is loaded
-// and the row FFT takes the X it returns (P1 fused into P4).
-// items: {prob, first line, -, -}; CELLS/K lines per workgroup.  The row passes (P4, P9) use
-// several lines per workgroup so that their transposed accesses to `half` cover whole cache
-// lines (four consecutive image rows per k2 in FP32).
+// of the row's pixels (kept in registers) -> primal step -> X -> forward row FFT -> half.
+// PM >= 0 (PASS 0 and 4): the primal step of mode PM runs on each pixel before the row FFT, which
+// takes the X it returns (P1 fused into P4).
+// items: {prob, first line, -, -}; CELLS/K lines per workgroup.
 template <typename R, int CELLS, int PASS, int PM = -1>
 __global__ void __launch_bounds__(CELLS / 2)
 fft_pass_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int src_slot, int dst_slot) {
-  __shared__ Cell<R> lds[CELLS];
+  __shared__ Cell<R> lds[CELLS + CELLS / 8];
   const int4 it = items[blockIdx.x];
   const ProbDesc& P = descs[it.x];
   if (halted(P)) return;                 // stopped by an adaptive run
-  const int n = P.n, K = P.K, h2 = n / 2;
+  const int n = P.n, K = P.K;
   const int lines = CELLS / K;
-  const int lgK = lg2(K), lgL = lg2(lines), lgN = lg2(n);   // all powers of two
+  const int lgK = lg2(K);                // all powers of two
   const int line0 = it.y;
   const R* __restrict__ s = (const R*)P.deapod;
-  Cell<R>* __restrict__ half = (Cell<R>*)P.half;
-  Cell<R>* __restrict__ grid = (Cell<R>*)P.grid;
-  const int nthr = CELLS / 2;
+  cplx<R>* __restrict__ half = (cplx<R>*)P.half;       // cell c, channel ch at 4 c + ch
+  cplx<R>* __restrict__ grid = (cplx<R>*)P.grid;
+  const cplx<R>* __restrict__ tw = (const cplx<R>*)P.twiddle;
+  constexpr int nthr = CELLS / 2;
+  // the thread's line, channel and cells tl + q K/8; the pixel its quad lane takes in the pointwise
+  // steps is that of the cell q = 0, 1, 6 or 7: column (k + n/2) mod K, since pixel j lies at
+  // grid index (j - n/2) mod K
+  const int ch = threadIdx.x & 3, grp = threadIdx.x >> 2;
+  const int l = grp >> (lgK - 3), tl = grp & ((K >> 3) - 1);
+  const int line = line0 + l, e = K >> 3;              // e = n / 4
+  cplx<R>* x = (cplx<R>*)lds + 4 * lds_cell(l * K);
+  const int col = tl + (ch < 2 ? ch + 2 : ch - 2) * e;
+  const bool live = line < (PASS == 1 || PASS == 2 ? K : n);
+  cplx<R> v[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) v[q] = cmk(R(0), R(0));
 
   // the partial-slot table and the slot-box unions of the gridding tiles this workgroup's lines
   // read (their tile rows and the rows before them), staged once so the per-cell gathers index LDS
@@ -207,19 +254,13 @@ fft_pass_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ ite
     }
     __syncthreads();
   }
-  // P9 + P1 + P4: the primal step's inputs of this thread's pixels (its cells q and q + nthr in
-  // the crop) are requested now, so their loads overlap the loads and the inverse FFT below
-  // (not with 1024 threads, whose 128 registers would spill them)
-  constexpr bool kPrefetch = PASS == 4 && PM >= 0 && CELLS <= 1024;
-  PrimalIn<R> pin[kPrefetch ? 2 : 1];
+  // P9 + P1 + P4: the primal step's inputs of the thread's pixel are requested now, so their loads
+  // overlap the loads and the inverse FFT below (not by FP64's 1024 threads, whose 128 registers
+  // would spill them)
+  constexpr bool kPrefetch = PASS == 4 && !(sizeof(R) == 8 && CELLS > 1024);
+  PrimalIn<R> pin;
   if constexpr (kPrefetch) {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int q = threadIdx.x + u * nthr;
-      const int l = q >> lgK, k = q & (K - 1), r = line0 + l;
-      const int col = (k < h2) ? k + h2 : ((k >= K - h2) ? k - (K - h2) : -1);
-      if (r < n && col >= 0) pin[u] = primal_load<R, (PM < 0 ? 0 : PM)>(P, r * n + col);
-    }
+    if (live) pin = primal_load<R, (PM < 0 ? 0 : PM)>(P, line * n + col);
   }
   // ---- load ----
   // (the FP64 kernel with 1024 threads, 128 registers, keeps the gather one pair at a time: the
@@ -278,52 +319,14 @@ fft_pass_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ ite
     for (int u = 0; u < 2; ++u) {
 #pragma unroll
       for (int ch = 0; ch < 4; ++ch) { c[u].s[ch].re *= gfac; c[u].s[ch].im *= gfac; }
-      lds[threadIdx.x + u * nthr] = c[u];
+      lds[lds_cell(threadIdx.x + u * nthr)] = c[u];
     }
   }
-  if constexpr (PASS == 1 || PASS >= 3) {
-    // both of the thread's cells are loaded before either is stored, so the two loads are in
-    // flight together (P5 reads half[k2][r] into line order; P9 and the fused row pass read it
-    // transposed into their rows)
-    Cell<R> cv[2];
-    int dst[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int q = threadIdx.x + u * nthr;
-      cv[u] = zero_cell<R>();
-      if constexpr (PASS == 1) {
-        const int l = q >> lgK, k = q & (K - 1), k2 = line0 + l;
-        const int r = (k < h2) ? k + h2 : ((k >= K - h2) ? k - (K - h2) : -1);
-        if (k2 < K && r >= 0) cv[u] = half[(size_t)k2 * n + r];
-        dst[u] = q;
-      } else {
-        const int k2 = q >> lgL, l = q & (lines - 1), r = line0 + l;
-        if (r < n) cv[u] = half[(size_t)k2 * n + r];
-        dst[u] = l * K + k2;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) lds[dst[u]] = cv[u];
-  }
-  // P4 (the rows of X, or with PM the primal step's X, staged as they are computed), and P8's
-  // gathers one (cell, tile) pair at a time where the rounds above would spill
-  if constexpr (PASS == 0 || (PASS == 2 && !kRounds)) {
-  for (int q = threadIdx.x; q < lines * K; q += nthr) {
-    Cell<R> c = zero_cell<R>();
-    if (PASS == 0) {
-      const int l = q >> lgK, k = q & (K - 1), r = line0 + l;
-      const int col = (k < h2) ? k + h2 : ((k >= K - h2) ? k - (K - h2) : -1);
-      if (r < n && col >= 0) {
-        V4<R> v;
-        if (PM >= 0) v = primal_pixel<R, (PM < 0 ? 0 : PM)>(P, r * n + col);
-        else v = ((const V4<R>*)P.img[src_slot])[(size_t)r * n + col];
-        const R sc = s[r] * s[col];
-        c.s[0].re = v.x * sc; c.s[1].re = v.y * sc; c.s[2].re = v.z * sc; c.s[3].re = v.w * sc;
-      }
-      lds[q] = c;
-    } else {
+  if constexpr (PASS == 2 && !kRounds) {
+    for (int q = threadIdx.x; q < CELLS; q += nthr) {
+      Cell<R> c = zero_cell<R>();
       // the gathers one (cell, tile) pair at a time, in the order of the rounds above
-      const int l = q >> lgK, k = q & (K - 1), k2 = line0 + l;
+      const int ql = q >> lgK, k = q & (K - 1), k2 = line0 + ql;
       if (k2 < K) {
         const int ntg = P.ntile_side_g, RG = kGridTile + P.T - 1;
         const int t1 = k / kGridTile, t2 = k2 / kGridTile, a1 = k - t1 * kGridTile, a2 = k2 - t2 * kGridTile;
@@ -354,74 +357,80 @@ fft_pass_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ ite
 #pragma unroll
         for (int ch = 0; ch < 4; ++ch) { c.s[ch].re *= gfac; c.s[ch].im *= gfac; }
       }
-      lds[q] = c;
+      lds[lds_cell(q)] = c;
     }
   }
-  }
-  __syncthreads();
-  // lines * K == CELLS (K divides CELLS), so every thread owns one channel of 8 cells
-  fft_lines<R, CELLS>(lds, K, PASS >= 2, (const cplx<R>*)P.twiddle);
-
-  if constexpr (PASS == 4) {
-    // crop, Z^dagger and Re give Re phi^dagger B at the row's pixels; the primal step takes it
-    // and its X, deapodised and zero-padded, replaces the row in place (a pixel's crop position
-    // and its zero-padding position are the same cell)
-    static_assert(CELLS == 2 * (CELLS / 2), "two cells per thread");
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int q = threadIdx.x + u * nthr;
-      const int l = q >> lgK, k = q & (K - 1), r = line0 + l;
-      const int col = (k < h2) ? k + h2 : ((k >= K - h2) ? k - (K - h2) : -1);
-      Cell<R> c = zero_cell<R>();
-      if (r < n && col >= 0) {
-        const Cell<R> v = lds[q];
-        const R sc = s[r] * s[col];
-        // rounded products, not contracted into the primal step's sums: the result is bitwise
-        // the one of the separate passes, which store Re phi^dagger B and read it back
-        V4<R> g;
-        g.x = mul_rn(v.s[0].re, sc); g.y = mul_rn(v.s[1].re, sc);
-        g.z = mul_rn(v.s[2].re, sc); g.w = mul_rn(v.s[3].re, sc);
-        constexpr int PMM = PM < 0 ? 0 : PM;
-        const V4<R> x = kPrefetch ? primal_pixel_in<R, PMM>(P, r * n + col, g, pin[kPrefetch ? u : 0])
-                                  : primal_pixel_g<R, PMM>(P, r * n + col, g);
-        c.s[0].re = x.x * sc; c.s[1].re = x.y * sc; c.s[2].re = x.z * sc; c.s[3].re = x.w * sc;
-      }
-      lds[q] = c;
-    }
+  if constexpr (PASS == 2) {
     __syncthreads();
-    fft_lines<R, CELLS>(lds, K, false, (const cplx<R>*)P.twiddle);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = x[4 * lds_cell(tl + q * e) + ch];
+  }
+  // (cells 0 and 1 hold rows n/2 .., cells 6 and 7 rows 0 .. of the half-transformed columns)
+  if constexpr (PASS == 1) {
+    if (live) {
+      const cplx<R>* h = half + 4 * ((size_t)line * n + tl) + ch;
+      v[0] = h[4 * (2 * e)]; v[1] = h[4 * (3 * e)]; v[6] = h[0]; v[7] = h[4 * e];
+    }
+  }
+  if constexpr (PASS >= 3) {
+    if (live) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = half[4 * ((size_t)(tl + q * e) * n + line) + ch];
+    }
+  }
+  // P4: the thread's pixel of X (with PM the primal step's X), deapodised
+  const R sc = (PASS == 0 || PASS >= 3) && live ? s[line] * s[col] : R(0);
+  if constexpr (PASS == 0) {
+    R a[4] = {R(0), R(0), R(0), R(0)};
+    if (live) {
+      V4<R> p;
+      if constexpr (PM >= 0) p = primal_pixel<R, (PM < 0 ? 0 : PM)>(P, line * n + col);
+      else p = ((const V4<R>*)P.img[src_slot])[(size_t)line * n + col];
+      a[0] = p.x * sc; a[1] = p.y * sc; a[2] = p.z * sc; a[3] = p.w * sc;
+    }
+    quad_transpose(a);
+    v[0].re = a[0]; v[1].re = a[1]; v[6].re = a[2]; v[7].re = a[3];
+  }
+  fft_line<R, PASS >= 2>(v, x, lgK, tl, ch, tw);
+
+  if constexpr (PASS >= 3) {
+    // crop, Z^dagger and Re give Re phi^dagger B at the thread's pixel (rounded products, not
+    // contracted into the primal step's sums: the result is bitwise the one of the separate
+    // passes, which store Re phi^dagger B and read it back)
+    R a[4] = {v[0].re, v[1].re, v[6].re, v[7].re};
+    quad_transpose(a);
+    V4<R> g;
+    g.x = mul_rn(a[0], sc); g.y = mul_rn(a[1], sc); g.z = mul_rn(a[2], sc); g.w = mul_rn(a[3], sc);
+    if constexpr (PASS == 3) {
+      if (live) ((V4<R>*)P.img[dst_slot])[(size_t)line * n + col] = g;
+      return;
+    } else {
+      // the primal step takes it, and its X, deapodised and zero-padded, is the row's new input
+      a[0] = a[1] = a[2] = a[3] = R(0);
+      if (live) {
+        if constexpr (!kPrefetch) pin = primal_load<R, (PM < 0 ? 0 : PM)>(P, line * n + col);
+        const V4<R> p = primal_pixel_in<R, (PM < 0 ? 0 : PM)>(P, line * n + col, g, pin);
+        a[0] = p.x * sc; a[1] = p.y * sc; a[2] = p.z * sc; a[3] = p.w * sc;
+      }
+      quad_transpose(a);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = cmk(R(0), R(0));
+      v[0].re = a[0]; v[1].re = a[1]; v[6].re = a[2]; v[7].re = a[3];
+      fft_line<R, false>(v, x, lgK, tl, ch, tw);
+    }
   }
 
   // ---- store ----
-  if (PASS == 0 || PASS == 4) {
-    for (int q = threadIdx.x; q < lines * K; q += nthr) {
-      const int k2 = q >> lgL, l = q & (lines - 1), r = line0 + l;
-      if (r < n) half[(size_t)k2 * n + r] = lds[l * K + k2];
-    }
-  } else if (PASS == 1) {
-    for (int q = threadIdx.x; q < lines * K; q += nthr) {
-      const int l = q >> lgK, k1 = q & (K - 1), k2 = line0 + l;
-      if (k2 < K) grid[(size_t)k2 * K + k1] = lds[q];
-    }
-  } else if (PASS == 2) {
-    for (int q = threadIdx.x; q < lines * n; q += nthr) {
-      const int l = q >> lgN, r = q & (n - 1), k2 = line0 + l;
-      const int pos = r < h2 ? r + (K - h2) : r - h2;        // (r - n/2) mod K
-      if (k2 < K) half[(size_t)k2 * n + r] = lds[l * K + pos];
-    }
+  if (!live) return;
+  if constexpr (PASS == 0 || PASS == 4) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) half[4 * ((size_t)(tl + q * e) * n + line) + ch] = v[q];
+  } else if constexpr (PASS == 1) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) grid[4 * ((size_t)line * K + tl + q * e) + ch] = v[q];
   } else {
-    V4<R>* __restrict__ out = (V4<R>*)P.img[dst_slot];
-    for (int q = threadIdx.x; q < lines * n; q += nthr) {
-      const int l = q >> lgN, c = q & (n - 1), r = line0 + l;
-      const int pos = c < h2 ? c + (K - h2) : c - h2;
-      if (r < n) {
-        const Cell<R> v = lds[l * K + pos];
-        const R sc = s[r] * s[c];
-        V4<R> o;
-        o.x = v.s[0].re * sc; o.y = v.s[1].re * sc; o.z = v.s[2].re * sc; o.w = v.s[3].re * sc;
-        out[(size_t)r * n + c] = o;
-      }
-    }
+    cplx<R>* h = half + 4 * ((size_t)line * n + tl) + ch;
+    h[4 * (2 * e)] = v[0]; h[4 * (3 * e)] = v[1]; h[0] = v[6]; h[4 * e] = v[7];
   }
 }
 
