@@ -117,6 +117,7 @@ static_assert(sizeof(GlobalPtr<void>) == sizeof(void*), "one layout on the host 
 // Per-problem descriptor.  Pointers are typed by the engine's real type R.
 struct ProbDesc {
   int n, K, T, levels;
+  int fused_vis;         // P6 and P7 of the iterations beside a SARA branch run as the fused pass
   int nbases, has_dirac, nwav, ts;      // ts = grid tile side
   int ntile_side, deg, n_p6, gen_stride;
   int ntile_side_g;       // gridding tiles per side (side kGridTile)

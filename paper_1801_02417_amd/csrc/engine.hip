@@ -178,6 +178,14 @@ void check_tuning(const Tuning& t, int K) {
     throw Error(PSARA_EINVAL, "fft_cells must be 0 or 512, 1024 or 2048, and at least the grid side 2n");
 }
 
+// Whether a problem's iterations beside a SARA branch run P6 and P7 as one fused pass.  Alone the
+// fused pass is the faster, but its large workgroups share the CUs badly with SARA kernels on
+// another stream (256^2: 5 % slower than the two passes); as one of the paired launches, which a
+// branch with at most one analysis level before the coarse ones takes, it stays the faster.  By
+// the problem and not by the launch, so that a member of a batch, whose launches may be another's,
+// computes what it computes alone.
+static bool fused_vis(int levels, int c_level) { return levels < 2 || c_level <= 2; }
+
 // ------------------------------------------------------------------------------------------------
 // work lists (appended per problem, so batches concatenate them)
 
@@ -407,6 +415,7 @@ Engine<R>::Engine(const Geometry& g, hipStream_t stream) : geo_(g), s0_(stream) 
   for (int j = 0; j < n; ++j) s[j] = 1.0 / kb_hat(g.T, g.beta, (double)(j - n / 2) / (double)K);
   h_.deapod = upload_conv(s.data(), n);
   set_grid_kernel_limits<R>(g.ts, g.T);
+  set_pair_kernel_limits<R>();
   h_.dg_item = tuning_.degrid_item;
   h_.ana_wide = tuning_.ana_wide;
   // items of the operator passes
@@ -594,6 +603,7 @@ void Engine<R>::upload_items() {
   pl_.grid_ce = geo_.chunk_entries;
   pl_.sparse = h_.coef[COEF_A] != nullptr && h_.nwav > 0;
   pl_.tv = h_.tv_kind != 0;
+  pl_.vis = h_.fused_vis ? VisRoute::kFused : VisRoute::kSplit;
 }
 
 template <typename R>
@@ -733,6 +743,7 @@ void Engine<R>::set_prior(uint32_t mask, int levels, const double* weights, doub
   copy_sync(h_.coef[COEF_GW], gw.data(), gw.size() * sizeof(R), hipMemcpyHostToDevice, s0_, "weights upload");
   zero(h_.coef[COEF_A], coef_elems_ * sizeof(V4<R>));
   c_level_ = coarse_level<R>(n, levels);
+  h_.fused_vis = fused_vis(levels, c_level_) ? 1 : 0;
   build_prior_items();
   realloc_partials();
   upload_items();
@@ -794,28 +805,67 @@ void launch_sara_dual(const PassLists& L, hipStream_t s) {
   launch_synthesis_final<R>(lists_la(L, L.synfinal, s), COEF_A, IMG_PSIA, 0, IMG_PSIA2);
 }
 
-// Whether the iterations of `mode` run P6 and P7 as one fused pass: only when no SARA branch runs
-// beside them (the initialisation stage, Algorithm 3).  Alone the fused pass is the faster
-// (one launch, 50 against 26 + 32 us on the 256^2 / 2e5 workload), but beside the SARA kernels
-// its large workgroups share the CUs worse than the two separate passes, and the iteration is
-// about 5 % slower with it.
-inline bool fused_p6_p7(const PassLists& L, int mode) { return pm_tv(mode) || mode == PM_INIT || !L.sparse; }
+// Whether the prior's branch runs inside the data branch's launches (kernels_pair.hip) rather
+// than on a stream of its own: where it has no more stages than the data branch has passes
+// between the row passes (every problem's SARA branch by fused_vis(), and the TV priors).
+//   us per iteration, apart -> paired: 32^2 FP64 50.4 -> 46.6, 64^2 41.9 -> 37.6, 128^2 51.5 ->
+//   47.9, TV at 256^2 76.0 -> 65.7.  With two analysis levels, as P5 | level 1, P6 | level 2,
+//   P7 | coarse, P8 | level 2, the final synthesis alone: 256^2 94.3 -> 97.9, 128^2 FP64 71.1 ->
+//   83.4, since every pair waits for the longer of its two and the fused P6 + P7 has no place.
+// The pair kernels exist for 512 FFT cells per workgroup, and not for the all-bases tiling.
+inline bool paired(const PassLists& L, int mode) {
+  if (L.cells != 512) return false;
+  if (pm_tv(mode)) return true;
+  return mode != PM_INIT && L.sparse && L.vis == VisRoute::kFused && !(L.ana_wide & kAnaAllBases);
+}
+
+// How the iterations of `mode` run P6 and P7: fused where no SARA branch runs beside them (the
+// initialisation stage, Algorithm 3), else as each problem's fused_vis says
+inline VisRoute vis_route(const PassLists& L, int mode) {
+  return pm_tv(mode) || mode == PM_INIT || !L.sparse ? VisRoute::kFused : L.vis;
+}
 
 // P6, P7 and P8 of one iteration (the dual B step or Algorithm 3's residual, its gridding, and
 // the column inverse FFT, which takes the factor of the gridded values from the partials of the
 // fused pass, as one for the TV residual, or as the grid pass stored it)
 template <typename R>
-void launch_p6_p8(const PassLists& L, int mode, hipStream_t s) {
-  const bool tvm = pm_tv(mode);
-  if (fused_p6_p7(L, mode)) {
-    if (tvm) launch_degrid_grid<R>(GR_STOKES, lists_la(L, L.p7f, s), L.taps, VIS_Y, VIS_R);
-    else launch_degrid_grid<R>(GR_DUAL, lists_la(L, L.p7f, s), L.taps, VIS_BV, VIS_BV);
-    launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, tvm ? 2 : 1, 0);
-  } else {
+void launch_p6_p7(const PassLists& L, int mode, hipStream_t s) {
+  if (pm_tv(mode)) {
+    launch_degrid_grid<R>(GR_STOKES, lists_la(L, L.p7f, s), L.taps, VIS_Y, VIS_R);
+    return;
+  }
+  const VisRoute v = vis_route(L, mode);
+  if (v == VisRoute::kFused) {
+    launch_degrid_grid<R>(GR_DUAL, lists_la(L, L.p7f, s), L.taps, VIS_BV, VIS_BV);
+  } else if (v == VisRoute::kSplit) {
     launch_degrid<R>(DG_DUAL, lists_la(L, L.p6, s), L.max_ts, L.taps, VIS_BV, VIS_BV);
     launch_grid<R>(GR_DUAL, lists_la(L, L.p7, s), L.taps, VIS_BV, 0);
-    launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, 0, 0);
+  } else {
+    launch_degrid<R>(DG_DUAL, lists_la(L, L.p6s, s), L.max_ts, L.taps, VIS_BV, VIS_BV);
+    launch_grid_mixed<R>(lists_la(L, L.p7m, s), L.taps);
   }
+}
+
+template <typename R>
+void launch_p8(const PassLists& L, int mode, hipStream_t s) {
+  const VisRoute v = vis_route(L, mode);
+  const int factor = pm_tv(mode) ? 2 : v == VisRoute::kMixed ? 3 : v == VisRoute::kFused ? 1 : 0;
+  launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, factor, 0);
+}
+
+// The passes of one iteration between the row passes, the prior's stages beside them
+template <typename R>
+void launch_paired(const PassLists& L, int mode, hipStream_t s) {
+  auto la = [&](const DevItems& d) { return lists_la(L, d, s); };
+  if (pm_tv(mode)) {
+    launch_p5_tv_dual<R>(la(L.cols), la(L.img));
+    launch_degrid_grid<R>(GR_STOKES, la(L.p7f), L.taps, VIS_Y, VIS_R);
+    launch_p8_tv_synth<R>(la(L.cols), la(L.img));
+    return;
+  }
+  launch_p5_analysis<R>(la(L.cols), la(L.ana_d[1]));
+  launch_grid_coarse<R>(la(L.p7f), la(L.coarse), L.taps);
+  launch_p8_synthesis<R>(la(L.cols), la(L.synfinal));
 }
 
 template <typename R>
@@ -829,23 +879,29 @@ void launch_iterations(const PassLists& L, int mode, int count, hipStream_t s0, 
   // transforms S_new): residual Phi S - Y L^{-1} per Stokes map, gridded without mixing
   const bool tvm = pm_tv(mode);
   const bool sparse = tvm || ((mode != PM_INIT) && L.sparse);
+  const bool pair = sparse && paired(L, mode);
   for (int k = 0; k < count; ++k) {
-    // P5 is captured before the other branch's launches (it depends on the same row pass): the
-    // graph then issues it first, and the branch with less slack starts earlier
-    if (sparse) hip_check(hipEventRecord(fork, s0), "event record");
-    launch_fft<R>(1, lists_la(L, L.cols, s0), L.cells, 0, 0);                        // P5
-    if (sparse) {
-      hip_check(hipStreamWaitEvent(s1, fork, 0), "stream wait");
-      if (tvm) {
-        launch_tv_dual<R>(lists_la(L, L.img, s1));
-        launch_tv_synth<R>(lists_la(L, L.img, s1));
-      } else {
-        launch_sara_dual<R>(L, s1);
+    if (pair) {
+      launch_paired<R>(L, mode, s0);
+    } else {
+      // P5 is captured before the other branch's launches (it depends on the same row pass): the
+      // graph then issues it first, and the branch with less slack starts earlier
+      if (sparse) hip_check(hipEventRecord(fork, s0), "event record");
+      launch_fft<R>(1, lists_la(L, L.cols, s0), L.cells, 0, 0);                      // P5
+      if (sparse) {
+        hip_check(hipStreamWaitEvent(s1, fork, 0), "stream wait");
+        if (tvm) {
+          launch_tv_dual<R>(lists_la(L, L.img, s1));
+          launch_tv_synth<R>(lists_la(L, L.img, s1));
+        } else {
+          launch_sara_dual<R>(L, s1);
+        }
+        hip_check(hipEventRecord(join, s1), "event record");
       }
-      hip_check(hipEventRecord(join, s1), "event record");
+      launch_p6_p7<R>(L, mode, s0);
+      launch_p8<R>(L, mode, s0);
+      if (sparse) hip_check(hipStreamWaitEvent(s0, join, 0), "stream wait");
     }
-    launch_p6_p8<R>(L, mode, s0);
-    if (sparse) hip_check(hipStreamWaitEvent(s0, join, 0), "stream wait");
     if (k + 1 < count) launch_fused_rows<R>(mode, lists_la(L, L.rows, s0), L.rcells);  // P9 + next P1, P4
     else launch_fft<R>(3, lists_la(L, L.rows, s0), L.rcells, 0, IMG_PHIB);          // P9
   }
@@ -1388,25 +1444,31 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
   for (int i = 0; i <= NP; ++i) hip_check(hipEventCreate(&ev[i]), "event");
   for (int i = 0; i <= NP + 1; ++i) ms[i] = 0.0;
   const bool sparse = (mode != PM_INIT) && L.sparse;
-  auto p5_p8 = [&](bool timed) {
+  // P5 .. P8 with P6 and P7 timed as two passes; where the iterations run them fused, the two work
+  // on copies (VIS_R is scratch, the plain gridding leaves the l2-ball factor alone), and the passes
+  // that count follow untimed, so the state advances as the iterations advance it
+  const VisRoute route = vis_route(L, mode);
+  const bool fused = route == VisRoute::kFused;
+  auto p5_p8 = [&]() {
     launch_fft<R>(1, lists_la(L, L.cols, s), L.cells, 0, 0);
-    if (timed) hip_check(hipEventRecord(ev[5], s), "event record");
-    launch_degrid<R>(DG_DUAL, lists_la(L, L.p6, s), L.max_ts, L.taps, VIS_BV, VIS_BV);
-    if (timed) hip_check(hipEventRecord(ev[6], s), "event record");
-    launch_grid<R>(GR_DUAL, lists_la(L, L.p7, s), L.taps, VIS_BV, 0);
-    if (timed) hip_check(hipEventRecord(ev[7], s), "event record");
-    launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, 0, 0);
-    if (timed) hip_check(hipEventRecord(ev[8], s), "event record");
+    hip_check(hipEventRecord(ev[5], s), "event record");
+    const bool split = route == VisRoute::kSplit;
+    launch_degrid<R>(DG_DUAL, lists_la(L, L.p6, s), L.max_ts, L.taps, VIS_BV, split ? VIS_BV : VIS_R);
+    hip_check(hipEventRecord(ev[6], s), "event record");
+    launch_grid<R>(split ? GR_DUAL : GR_PLAIN, lists_la(L, L.p7, s), L.taps, split ? VIS_BV : VIS_R, 0);
+    hip_check(hipEventRecord(ev[7], s), "event record");
+    if (!split) launch_p6_p7<R>(L, mode, s);
+    hip_check(hipEventRecord(ev[3], s), "event record");
+    launch_p8<R>(L, mode, s);
+    hip_check(hipEventRecord(ev[8], s), "event record");
   };
   // P5 .. P8 as the iterations run them, with the fused P6 + P7 pass timed where they use it
-  const bool fused = fused_p6_p7(L, mode);
   auto p5_p8_run = [&]() {
     launch_fft<R>(1, lists_la(L, L.cols, s), L.cells, 0, 0);
     hip_check(hipEventRecord(ev[2], s), "event record");
-    if (fused) launch_degrid_grid<R>(GR_DUAL, lists_la(L, L.p7f, s), L.taps, VIS_BV, VIS_BV);
+    launch_p6_p7<R>(L, mode, s);
     hip_check(hipEventRecord(ev[3], s), "event record");
-    if (fused) launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, 1, 0);
-    else launch_p6_p8<R>(L, mode, s);
+    launch_p8<R>(L, mode, s);
   };
   for (int k = 0; k < iters; ++k) {
     hip_check(hipEventRecord(ev[0], s), "event record");
@@ -1414,14 +1476,14 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
     hip_check(hipEventRecord(ev[1], s), "event record");
     if (sparse) launch_sara_dual<R>(L, s);   // P2 and P3 with the fused coarse levels: timed as P2
     hip_check(hipEventRecord(ev[2], s), "event record");
-    p5_p8(true);
+    p5_p8();
     launch_fft<R>(3, lists_la(L, L.rows, s), L.rcells, 0, IMG_PHIB);
     hip_check(hipEventRecord(ev[9], s), "event record");
     hip_check(hipEventSynchronize(ev[9]), "event sync");
     for (int i = 0; i < NP; ++i) {
       if (i == 2 || i == 3) continue;          // P3 runs inside P2's launches, P4 inside P1's
       float t = 0.f;
-      hip_check(hipEventElapsedTime(&t, ev[i == 4 ? 2 : i], ev[i + 1]), "elapsed");
+      hip_check(hipEventElapsedTime(&t, ev[i == 4 ? 2 : i == 7 ? 3 : i], ev[i + 1]), "elapsed");
       ms[i] += t;
     }
   }
@@ -1530,7 +1592,27 @@ Batch<R>::Batch(const std::vector<Engine<R>*>& members, hipStream_t stream) : me
   pl_.ana_wide = ana_wide;
   pl_.grid_ce = grid_ce;
   pl_.sparse = sparse;
+  // the members whose main iterations run P6 and P7 fused, and the others
+  auto part = [&](const std::vector<int4>& v, int fused) {
+    std::vector<int4> o;
+    for (const int4& it : v)
+      if (members_[it.x]->desc().fused_vis == fused) o.push_back(it);
+    return o;
+  };
+  size_t fused = 0;
+  for (Engine<R>* e : members_) fused += e->desc().fused_vis != 0;
+  pl_.vis = fused == members_.size() ? VisRoute::kFused : fused ? VisRoute::kMixed : VisRoute::kSplit;
+  if (pl_.vis == VisRoute::kMixed) {
+    std::vector<int4> p6s = part(S.p6, 0);
+    order_degrid_items(p6s.begin(), p6s.end());
+    std::vector<int4> p7m = part(S.p7, 0);
+    for (const int4& it : part(S.p7f, 1))
+      if (it.y >= 0) p7m.push_back(it);
+    order_grid_items(p7m.begin(), p7m.end(), [this](int prob) { return &members_[prob]->geometry(); });
+    up(pl_.p6s, p6s); up(pl_.p7m, p7m);
+  }
   set_grid_kernel_limits<R>(max_ts, T);
+  set_pair_kernel_limits<R>();
   hip_check(hipStreamCreateWithFlags(&s1_, hipStreamNonBlocking), "hipStreamCreate");
   hip_check(hipEventCreateWithFlags(&ev_fork_, hipEventDisableTiming), "hipEventCreate");
   hip_check(hipEventCreateWithFlags(&ev_join_, hipEventDisableTiming), "hipEventCreate");

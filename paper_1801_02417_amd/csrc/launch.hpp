@@ -36,7 +36,8 @@ enum DegridMode { DG_DUAL = 0, DG_FORWARD = 1, DG_RESIDUAL = 2, DG_STOKES = 3 };
 enum GridMode { GR_DUAL = 0, GR_PLAIN = 1, GR_STOKES = 2 };
 
 // pass 2 (P8) takes src_slot as the factor mode of the gridded values: 0 the factor the grid
-// pass stored, 1 the l2-ball factor of the fused pass's partials, 2 one
+// pass stored, 1 the l2-ball factor of the fused pass's partials, 2 one, 3 one of the first two by
+// the problem's fused_vis
 template <typename R> void launch_fft(int pass, const LaunchArgs& a, int cells, int src_slot, int dst_slot);
 template <typename R> void launch_primal_fft(int mode, const LaunchArgs& a, int cells);
 // P9 of one iteration with P1 and P4 of the next (row work list)
@@ -47,6 +48,9 @@ template <typename R> void launch_grid(int mode, const LaunchArgs& a, int taps, 
 // the dual B step, then grid Bv; GR_STOKES: Algorithm 3's residual, then grid it); the column
 // inverse FFT after it takes factor mode 1 (GR_DUAL) or 2 (GR_STOKES)
 template <typename R> void launch_degrid_grid(int mode, const LaunchArgs& a, int taps, int src_slot, int out_slot);
+// P7 (GR_DUAL) of the problems that run P6 and P7 as two passes and the fused pass of the others
+// (ProbDesc::fused_vis), in one launch
+template <typename R> void launch_grid_mixed(const LaunchArgs& a, int taps);
 template <typename R> void set_grid_kernel_limits(int max_ts, int taps);
 void hip_check(hipError_t e, const char* what);
 template <typename R> void launch_primal(int mode, const LaunchArgs& a);
@@ -71,6 +75,14 @@ template <typename R> void launch_fill(void* p, size_t count, hipStream_t s);
 template <typename R> void launch_tv_dual(const LaunchArgs& a);
 template <typename R> void launch_tv_synth(const LaunchArgs& a);
 template <typename R> void launch_tv_objective(const LaunchArgs& a);
+// Two passes in one launch: items of the data branch (a) beside items of the prior branch (b),
+// with 512 FFT cells per workgroup
+template <typename R> void launch_p5_analysis(const LaunchArgs& a, const LaunchArgs& b);   // P5, the first level
+template <typename R> void launch_grid_coarse(const LaunchArgs& a, const LaunchArgs& b, int taps);   // P6 + P7, coarse
+template <typename R> void launch_p8_synthesis(const LaunchArgs& a, const LaunchArgs& b);  // P8, the final synthesis
+template <typename R> void launch_p5_tv_dual(const LaunchArgs& a, const LaunchArgs& b);
+template <typename R> void launch_p8_tv_synth(const LaunchArgs& a, const LaunchArgs& b);
+template <typename R> void set_pair_kernel_limits();   // once per device, outside any capture
 // finalise: one workgroup per problem sums PART_GEN partials into scal[scalar]
 void launch_finalize(const ProbDesc* descs, int nprob, int region, int count, int scalar, hipStream_t s);
 void launch_finalize_zeta(const ProbDesc* descs, int nprob, hipStream_t s);
