@@ -270,7 +270,8 @@ psara_status psara_set_gamma(psara_ctx* ctx, double gamma);
  * summation order of the gridding and of the de-gridding norm (results differ at rounding level,
  * never in what is computed); every solve starts with the defaults. */
 typedef struct {
-    int grid_chunk;      /* gridding entries per workgroup: 256, 512 or 1024 (default 1024) */
+    int grid_chunk;      /* gridding entries per workgroup: 256, 512 or 1024 (default 1024, which
+                            a problem too small to fill the GPU cuts down to 64 or more) */
     int degrid_item;     /* visibilities per de-gridding workgroup: a power of two in [64, 1024]
                             (default 256) */
     int analysis_wide;   /* bit 0: 16-wide output tiles for the analysis bands of side >= 128 of

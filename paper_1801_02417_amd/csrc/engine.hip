@@ -105,11 +105,43 @@ Geometry build_geometry(int n, int64_t M, const double* uv, int alpha, int T) {
   return g;
 }
 
-void build_grid_chunks(Geometry& g, int chunk_entries) {
+// The entries the chunks are cut for.  The default asks for the smallest size at which no tile
+// has more than kMaxTileChunks chunks and all chunks together are at most kMaxSmallChunks (two
+// workgroups per CU): a problem that does not fill the GPU is bound by its longest chunk, and the
+// column inverse FFT, which adds a tile's slots one after the other, by the tile with the most.
+// Another size is taken as asked for.
+//   us per iteration at 1024, 512, 256, 128, 64 entries (most chunks of one tile):
+//   32^2 FP64, 600 rows   46.5 46.4 46.4 42.5 39.6  (1 1 1 2 4)
+//   64^2 FP32, 1511 rows  37.6 37.6 37.6 37.3 35.1  (1 1 1 2 3)
+//   64^2 FP64, 3000 rows  70.0 67.4 56.2 55.6 60.5  (1 2 3 5 9)
+//   128^2 FP32, 12000     47.8 44.4 42.3 43.7 48.0  (1 2 3 6 11)
+//   128^2 FP32 with Mueller matrices, 20001   57.4 at 1024, 44.9 at 256 (1, 4)
+//   64^2 FP32, 30000      52.7 48.7 54.0 74.0 115.7 (5 10 20 39 77)
+//   256^2 FP32, 2e5       94.9 95.7 100  126  182   (4 8 16 31 61; 848 chunks at 1024)
+int grid_chunk_entries(const Geometry& g, int asked) {
+  constexpr int kMaxTileChunks = 4, kMaxSmallChunks = 512, kLeast = 64;
+  static_assert(kRunMax <= kLeast, "a run fits a chunk");
+  int best = asked;
+  for (int c = asked / 2; asked == kChunkEntries && c >= kLeast; c /= 2) {
+    long long most = 0, all = 0;
+    for (size_t t = 0; t < g.row_beg.size(); ++t) {
+      const long long k = (g.row_end[t] - g.row_beg[t] + c - 1) / c;
+      most = std::max(most, k);
+      all += k;
+    }
+    if (most > kMaxTileChunks || all > kMaxSmallChunks) break;
+    best = c;
+  }
+  return best;
+}
+
+void build_grid_chunks(Geometry& g, int asked) {
   const int ntg = g.ntsg * g.ntsg;
+  const int chunk_entries = grid_chunk_entries(g, asked);
   g.run_pack.clear();
   g.chunks.clear(); g.chunk_ent.clear(); g.tile_slots.clear(); g.slot_box.clear(); g.tile_box.clear(); g.small_ids.clear();
   g.n_slots = 0;
+  g.chunk_asked = asked;
   g.chunk_entries = chunk_entries;
   // runs: consecutive rows of a tile with the same window start (their taps hit the
   // same cells), split at kRunMax; chunks of whole runs with <= chunk_entries entries, runs
@@ -557,7 +589,7 @@ void Engine<R>::set_tuning(const Tuning& t) {
   check_tuning(t, geo_.K);
   hip_check(hipStreamSynchronize(s0_), "tuning sync");
   hip_check(hipStreamSynchronize(s1_), "tuning sync");
-  if (t.grid_chunk != geo_.chunk_entries) {
+  if (t.grid_chunk != geo_.chunk_asked) {
     build_grid_chunks(geo_, t.grid_chunk);
     upload_chunks();
   }

@@ -39,12 +39,14 @@ struct Geometry {
   std::vector<int> tile_box;             // per gridding tile: the union of its slots' boxes
   std::vector<int> small_ids;            // chunks of at most kSmallChunk entries, heaviest first
   int n_slots = 0;
-  int chunk_entries = kChunkEntries;     // the chunk size the runs and chunks were cut for
+  int chunk_asked = kChunkEntries;       // the chunk size asked for (the tuning's grid_chunk)
+  int chunk_entries = kChunkEntries;     // and the one the runs and chunks were cut for
 };
 
 Geometry build_geometry(int n, int64_t M, const double* uv, int alpha, int T);
-// (Re)cuts the gridding lists of a geometry into runs and chunks of at most chunk_entries entries.
-void build_grid_chunks(Geometry& g, int chunk_entries);
+// (Re)cuts the gridding lists of a geometry into runs and chunks of at most `asked` entries (of
+// fewer, at the default, where the problem would not fill the GPU).
+void build_grid_chunks(Geometry& g, int asked);
 
 // Launch shapes of a solve that the autotuner chooses among (they change the summation order of
 // the gridding and the de-gridding norm, not what is computed).
