@@ -29,6 +29,7 @@ constexpr int kMaxDegridTile = 32;  // largest de-gridding tile side (the geomet
 // window with T = 8, 1.49 reads per grid cell against 2.07 for 16-cell tiles), 16 below
 constexpr int degrid_tile(int K) { return K >= 64 ? kMaxDegridTile : kMaxDegridTile / 2; }
 constexpr int kDegridItem = 256;        // default visibilities per de-gridding work item
+constexpr int kCoarseThreads = 512; // threads per workgroup of the coarse SARA levels
 constexpr int kGridTile = 16;       // side of the gridding tiles (the de-gridding tiles are P.ts)
 // analysis tiling (the analysis_wide tuning, a problem's ana_wide), two bits: kAnaWide, 16-wide
 // output tiles for FP32 bands of side >= 128 (else 8-wide); kAnaAllBases, level-1 items of the

@@ -177,13 +177,14 @@ __device__ inline AnaTile ana_tile(const ProbDesc& P, int level, int tile) {
 
 // Stages the in x in input elements of a tile (from row 2 o1, column 2 o2 of the m x m band src,
 // wrapped periodically) into sm.in as rows of in elements.
+// (all of a thread's loads are issued before its LDS stores, so they are in flight together)
 template <typename R, class Smem>
 __device__ inline void ana_stage(Smem& sm, const V4<R>* __restrict__ src, const AnaTile& g, int in) {
   const float rin = 1.0f / (float)in;
-  for (int q = threadIdx.x; q < in * in; q += blockDim.x) {
+  stage_lds<(Smem::IN * Smem::IN + 255) / 256>(sm.in, in * in, [&](int q) {
     const int a = small_div(q, rin), b = q - a * in;
-    sm.in[q] = src[(size_t)((2 * g.o1 + a) & (g.m - 1)) * g.m + ((2 * g.o2 + b) & (g.m - 1))];
-  }
+    return src[(size_t)((2 * g.o1 + a) & (g.m - 1)) * g.m + ((2 * g.o2 + b) & (g.m - 1))];
+  });
 }
 
 // One basis w over one output tile.  ins = 0: stages the tile's input for this filter first;
@@ -494,155 +495,164 @@ __device__ __forceinline__ void synthesis_final_item(const ProbDesc& P, const in
 
 // ---------------------------------------------------------------------------------------------
 // Coarse levels c..L of one wavelet basis and one Stokes channel in a single workgroup: the
-// low-low band entering level c (at most CoarseMax<R> on a side) is held in LDS; analysis runs
-// level by level with the dual update of every coefficient, which also stays in LDS as the
-// Mallat pyramid of the coarse levels; synthesis then runs back from level L to level c on
+// low-low band entering level c (at most CoarseMax<R> on a side) is held in LDS, where the
+// analysis turns it level by level into the Mallat pyramid of the coarse levels, in place; every
+// coefficient's dual update follows, and synthesis runs back in place from level L to level c on
 // the updated duals and leaves the low-low band of level c-1 in the level scratch, where the
 // next synthesis launch reads it.  Replaces 2 (L - c + 1) small launches by one.
 // items: {prob, wavelet index (-1: none), Stokes channel, first coarse level c}
-template <typename R> struct CoarseMax { static constexpr int value = sizeof(R) == 4 ? 64 : 32; };
+//
+// In place without a second buffer: a filter pass runs along lines (rows or columns) of m <= 128
+// elements, whose m/2 <= 64 outputs of each kind belong to the lanes of one wave step, so every
+// element of a line is read before the step writes the line, and no other wave touches it.  The
+// rows are padded by one element, so that column lines, too, spread over the LDS banks.
+//
+// FP32 holds 128 x 128 elements (66 KB, which the fused gridding launch it runs beside takes
+// anyway), so that a 256^2 image needs one analysis launch before it, not two, and its branch
+// fits the data branch's launches: 94.3 -> 84.8 us per iteration at 256^2 / 2e5 rows.  Bound by
+// one CU's work on a channel of 128^2: at 16 taps 5.6 us of loads, 11 of analysis, 8.6 of
+// updates, 10 of synthesis and 2 of stores; more loads in flight, filters that take the next
+// line's elements a step ahead and lanes spread over two lines for the banks gave nothing.
+// Larger images keep 64 x 64 (their branch runs beside the data branch's on another stream,
+// where a workgroup that long would be the longer one).
+template <typename R> struct CoarseMax { static constexpr int value = sizeof(R) == 4 ? 128 : 64; };
 
 template <typename R>
 __device__ inline R& chan(V4<R>& v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 
+// The filters of one step: lane output k of the line at b, reading the elements at offsets lo (for
+// SYN also those hi further on), with the outputs at offsets oa and ob.
+template <int F, bool SYN, typename R>
+__device__ __forceinline__ void coarse_step(R* b, const int* lo, int hi, int oa, int ob, const Taps<R, F>& t) {
+  R a0 = R(0), a1 = R(0);
+  if constexpr (SYN) {
+    R x[F / 2], y[F / 2];
+#pragma unroll
+    for (int j = 0; j < F / 2; ++j) { x[j] = b[lo[j]]; y[j] = b[lo[j] + hi]; }
+#pragma unroll
+    for (int j = 0; j < F / 2; ++j) {
+      a0 += t.h[2 * j] * x[j] + t.g[2 * j] * y[j];
+      a1 += t.h[2 * j + 1] * x[j] + t.g[2 * j + 1] * y[j];
+    }
+  } else {
+    R x[F];
+#pragma unroll
+    for (int j = 0; j < F; ++j) x[j] = b[lo[j]];
+#pragma unroll
+    for (int j = 0; j < F; ++j) { a0 += t.h[j] * x[j]; a1 += t.g[j] * x[j]; }
+  }
+  b[oa] = a0;
+  b[ob] = a1;
+}
+
+// One filter pass over the m lines of the top-left m x m block: element e of line l is
+// buf[l * SL + e * SE].  Analysis: low outputs to elements 0 .. h-1, high ones to h .. m-1
+// (h = m/2); synthesis: back, outputs 2k and 2k+1 through the even and the odd taps.  A lane
+// keeps its output index k over the steps, so the offsets of the elements it reads (wrapped
+// periodically) are worked out once.  The largest block, which takes three quarters of the time,
+// has its sizes as constants: four steps share the offsets' registers, their lines immediates.
+template <int F, bool SYN, int SL, int SE, typename R>
+__device__ __forceinline__ void coarse_lines(R* buf, int m, const Taps<R, F>& t) {
+  constexpr int M = CoarseMax<R>::value, NW = kCoarseThreads / 64;
+  const int h = m >> 1, lh = lg2(h), lane = threadIdx.x & 63;
+  const int per = 64 >> lh;                        // lines per wave step
+  const int k = lane & (h - 1), own = lane >> lh;  // this lane's output, and its line of the step
+  int lo[SYN ? F / 2 : F];
+#pragma unroll
+  for (int j = 0; j < (SYN ? F / 2 : F); ++j) lo[j] = own * SL + (SYN ? (k - j) & (h - 1) : (2 * k + j) & (m - 1)) * SE;
+  const int oa = own * SL + (SYN ? 2 * k : k) * SE;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (m == M) {
+    constexpr int PER = 128 / M, STEPS = M / (PER * NW), UN = STEPS < 4 ? STEPS : 4;
+    R* b = buf + wave * PER * SL;
+#pragma unroll 1
+    for (int i = 0; i < STEPS; i += UN, b += UN * NW * PER * SL)
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        coarse_step<F, SYN>(b + u * NW * PER * SL, lo, M / 2 * SE, oa, oa + (SYN ? 1 : M / 2) * SE, t);
+  } else {
+    for (int l0 = wave * per; l0 < m; l0 += NW * per)
+      if (l0 + own < m)                            // (blocks of fewer lines than a step's)
+        coarse_step<F, SYN>(buf + l0 * SL, lo, h * SE, oa, oa + (SYN ? 1 : h) * SE, t);
+  }
+  __syncthreads();
+}
+
 template <int F, typename R>
-__device__ __forceinline__ void coarse_body(const ProbDesc& P, int w, int ch, int c_level, R* bufA, R* bufB, R* pyr,
-                                            R* gw) {
+__device__ __forceinline__ void coarse_body(const ProbDesc& P, int w, int ch, int c_level, R* buf) {
   const Taps<R, F> t((const R*)P.filters + w * kMaxFilter);
-  const int n = P.n, L = P.levels, nt = blockDim.x;
-  R* __restrict__ ll = (R*)((V4<R>*)P.ll + (size_t)w * P.ll_stride);
+  const int n = P.n, L = P.levels;
+  R* __restrict__ ll = (R*)((V4<R>*)P.ll + (size_t)w * P.ll_stride + P.ll_off[c_level - 1]);
   R* __restrict__ A = (R*)((V4<R>*)P.coef[COEF_A] + (size_t)(P.has_dirac + w) * n * n);
   const R* __restrict__ GW = (const R*)((const V4<R>*)P.coef[COEF_GW] + (size_t)(P.has_dirac + w) * n * n);
   const R r1n = R(P.rho1) * R(P.norm);
-  const int m0 = n >> (c_level - 1);               // side of the coarse pyramid
-  int m = m0;
-  // every coarse band lies in the top-left m0 x m0 block of the basis: its duals (into pyr,
-  // where the updated ones are kept) and thresholds are staged with the low-low band, so the
-  // dual updates below read LDS only
-  // (each thread's loads are all issued before its LDS stores, so they are in flight together)
-  {
-    constexpr int NS = (CoarseMax<R>::value * CoarseMax<R>::value + 511) / 512;
-    R va[NS], vp[NS], vg[NS];
+  const int m0 = n >> (c_level - 1), lm = lg2(m0);   // side of the coarse pyramid
+  constexpr int s = CoarseMax<R>::value + 1;
+  // the low-low band in rounds of NB loads; the duals and thresholds of the coarse bands (the
+  // top-left m0 x m0 block of the basis) in rounds of NB, a round ahead of the updates that use
+  // them, the first one ahead of the filters
+  constexpr int NB = 8;
+  for (int q0 = threadIdx.x; q0 < m0 * m0; q0 += NB * kCoarseThreads) {
+    R v[NB];
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      const int q = threadIdx.x + u * nt;
-      if (q < m * m) {
-        const size_t g = (size_t)(q >> lg2(m0)) * n + (q & (m0 - 1));
-        va[u] = ll[4 * (P.ll_off[c_level - 1] + q) + ch];
-        vp[u] = A[4 * g + ch];
-        vg[u] = GW[4 * g + ch];
-      }
+    for (int u = 0; u < NB; ++u) {
+      const int q = q0 + u * kCoarseThreads;
+      if (q < m0 * m0) v[u] = ll[4 * q + ch];
     }
 #pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      const int q = threadIdx.x + u * nt;
-      if (q < m * m) {
-        bufA[q] = va[u];
-        pyr[q] = vp[u];
-        gw[q] = vg[u];
-      }
+    for (int u = 0; u < NB; ++u) {
+      const int q = q0 + u * kCoarseThreads;
+      if (q < m0 * m0) buf[(q >> lm) * s + (q & (m0 - 1))] = v[u];
     }
   }
+  auto fetch = [&](int q0, R* va, R* vg) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int q = q0 + u * kCoarseThreads;
+      const int g = 4 * ((q >> lm) * n + (q & (m0 - 1))) + ch;
+      if (q < m0 * m0) { va[u] = A[g]; vg[u] = GW[g]; }
+    }
+  };
+  R va[NB], vg[NB];
+  fetch(threadIdx.x, va, vg);
   __syncthreads();
-  // ---- analysis c..L (bufA holds the m x m low-low band) ----
-  for (int l = c_level; l <= L; ++l) {
-    const int h = m >> 1;
-    for (int q = threadIdx.x; q < m * h; q += nt) {          // rows: bufB[r][k] = a, bufB[r][h+k] = d
-      const int r = q >> lg2(h), k = q & (h - 1);
-      R sa = R(0), sd = R(0);
-#pragma unroll
-      for (int j = 0; j < F; ++j) {
-        const R x = bufA[r * m + ((2 * k + j) & (m - 1))];
-        sa += t.h[j] * x;
-        sd += t.g[j] * x;
-      }
-      bufB[r * m + k] = sa;
-      bufB[r * m + h + k] = sd;
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < h * m; q += nt) {          // columns; q = (k, col)
-      const int k = q >> lg2(m), col = q & (m - 1);
-      R ca = R(0), cd = R(0);
-#pragma unroll
-      for (int j = 0; j < F; ++j) {
-        const R x = bufB[((2 * k + j) & (m - 1)) * m + col];
-        ca += t.h[j] * x;
-        cd += t.g[j] * x;
-      }
-      // (k, col): low rows; (h + k, col): high rows
-      if (col < h && l < L) {
-        bufA[k * h + col] = ca;                              // next level's input
-      } else {
-        const int p = k * m0 + col;
-        const R a = fmin(fmax(pyr[p] + r1n * ca, -gw[p]), gw[p]);
-        A[4 * ((size_t)k * n + col) + ch] = a;
-        pyr[p] = a;
-      }
-      const int p = (h + k) * m0 + col;
-      const R d = fmin(fmax(pyr[p] + r1n * cd, -gw[p]), gw[p]);
-      A[4 * ((size_t)(h + k) * n + col) + ch] = d;
-      pyr[p] = d;
-    }
-    __syncthreads();
-    m = h;
+  for (int l = c_level, m = m0; l <= L; ++l, m >>= 1) {
+    coarse_lines<F, false, s, 1>(buf, m, t);       // rows
+    coarse_lines<F, false, 1, s>(buf, m, t);       // columns
   }
-  // ---- synthesis L..c on the updated duals (bufA: the h x h low-low input) ----
-  {
-    const int h = n >> L;
-    for (int q = threadIdx.x; q < h * h; q += nt) bufA[q] = pyr[(q >> lg2(h)) * m0 + (q & (h - 1))];
+  for (int q0 = threadIdx.x; q0 < m0 * m0; q0 += NB * kCoarseThreads) {
+    R na[NB], ng[NB];
+    fetch(q0 + NB * kCoarseThreads, na, ng);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      const int q = q0 + u * kCoarseThreads;
+      if (q < m0 * m0) {
+        R* x = buf + (q >> lm) * s + (q & (m0 - 1));
+        const R a = fmin(fmax(va[u] + r1n * *x, -vg[u]), vg[u]);
+        A[4 * ((q >> lm) * n + (q & (m0 - 1))) + ch] = a;
+        *x = a;
+      }
+      va[u] = na[u];
+      vg[u] = ng[u];
+    }
   }
   __syncthreads();
   for (int l = L; l >= c_level; --l) {
-    const int mo = n >> (l - 1), h = mo >> 1;
-    // inverse column transform: bufB[ir][b] (b < h) from LL/LH, bufB[mo*h + ir*h + b] from HL/HH;
-    // output rows 2r', 2r'+1 read the same coefficients through the even / odd taps
-    for (int q = threadIdx.x; q < h * h; q += nt) {
-      const int rp = q >> lg2(h), b = q & (h - 1);
-      R sa0 = R(0), sd0 = R(0), sa1 = R(0), sd1 = R(0);
-#pragma unroll
-      for (int jj = 0; jj < F / 2; ++jj) {
-        const int r = (rp - jj) & (h - 1);
-        const R ll = bufA[r * h + b], lh = pyr[(h + r) * m0 + b];
-        const R hl = pyr[r * m0 + h + b], hh = pyr[(h + r) * m0 + h + b];
-        sa0 += t.h[2 * jj] * ll + t.g[2 * jj] * lh;
-        sd0 += t.h[2 * jj] * hl + t.g[2 * jj] * hh;
-        sa1 += t.h[2 * jj + 1] * ll + t.g[2 * jj + 1] * lh;
-        sd1 += t.h[2 * jj + 1] * hl + t.g[2 * jj + 1] * hh;
-      }
-      bufB[(2 * rp) * h + b] = sa0;
-      bufB[mo * h + (2 * rp) * h + b] = sd0;
-      bufB[(2 * rp + 1) * h + b] = sa1;
-      bufB[mo * h + (2 * rp + 1) * h + b] = sd1;
-    }
-    __syncthreads();
-    // inverse row transform into bufA (mo x mo), column pairs
-    for (int q = threadIdx.x; q < mo * h; q += nt) {
-      const int ir = q >> lg2(h), cp = q & (h - 1);
-      R s0 = R(0), s1 = R(0);
-#pragma unroll
-      for (int jj = 0; jj < F / 2; ++jj) {
-        const int b = (cp - jj) & (h - 1);
-        const R ca = bufB[ir * h + b], cd = bufB[mo * h + ir * h + b];
-        s0 += t.h[2 * jj] * ca + t.g[2 * jj] * cd;
-        s1 += t.h[2 * jj + 1] * ca + t.g[2 * jj + 1] * cd;
-      }
-      bufA[ir * mo + 2 * cp] = s0;
-      bufA[ir * mo + 2 * cp + 1] = s1;
-    }
-    __syncthreads();
+    coarse_lines<F, true, 1, s>(buf, n >> (l - 1), t);
+    coarse_lines<F, true, s, 1>(buf, n >> (l - 1), t);
   }
-  for (int q = threadIdx.x; q < m0 * m0; q += nt) ll[4 * (P.ll_off[c_level - 1] + q) + ch] = bufA[q];
+  for (int q = threadIdx.x; q < m0 * m0; q += kCoarseThreads) ll[4 * q + ch] = buf[(q >> lm) * s + (q & (m0 - 1))];
 }
 
 template <typename R>
 struct CoarseSmem {
   static constexpr int MM = CoarseMax<R>::value;
-  R bufA[MM * MM], bufB[MM * MM], pyr[MM * MM], gw[MM * MM];
+  R buf[MM * (MM + 1)];
 };
 template <typename R>
 __device__ __forceinline__ void coarse_item(const ProbDesc& P, const int4 it, CoarseSmem<R>& sm) {
   if (halted(P) || it.y < 0) return;    // stopped by an adaptive run, or an empty basis place
-#define PSARA_COARSE(FF) coarse_body<FF, R>(P, it.y, it.z, it.w, sm.bufA, sm.bufB, sm.pyr, sm.gw)
+#define PSARA_COARSE(FF) coarse_body<FF, R>(P, it.y, it.z, it.w, sm.buf)
   PSARA_FILTER_SWITCH(P.wav_len[it.y], PSARA_COARSE)
 #undef PSARA_COARSE
 }

@@ -212,7 +212,7 @@ void check_tuning(const Tuning& t, int K) {
 
 // Whether a problem's iterations beside a SARA branch run P6 and P7 as one fused pass.  Alone the
 // fused pass is the faster, but its large workgroups share the CUs badly with SARA kernels on
-// another stream (256^2: 5 % slower than the two passes); as one of the paired launches, which a
+// another stream (256^2 there: 5 % slower than the two passes); as one of the paired launches, which a
 // branch with at most one analysis level before the coarse ones takes, it stays the faster.  By
 // the problem and not by the launch, so that a member of a batch, whose launches may be another's,
 // computes what it computes alone.
@@ -841,14 +841,20 @@ void launch_sara_dual(const PassLists& L, hipStream_t s) {
 // than on a stream of its own: where it has no more stages than the data branch has passes
 // between the row passes (every problem's SARA branch by fused_vis(), and the TV priors).
 //   us per iteration, apart -> paired: 32^2 FP64 50.4 -> 46.6, 64^2 41.9 -> 37.6, 128^2 51.5 ->
-//   47.9, TV at 256^2 76.0 -> 65.7.  With two analysis levels, as P5 | level 1, P6 | level 2,
-//   P7 | coarse, P8 | level 2, the final synthesis alone: 256^2 94.3 -> 97.9, 128^2 FP64 71.1 ->
-//   83.4, since every pair waits for the longer of its two and the fused P6 + P7 has no place.
-// The pair kernels exist for 512 FFT cells per workgroup, and not for the all-bases tiling.
+//   47.9, 256^2 94.3 -> 84.8, TV at 256^2 76.0 -> 65.7.  With two analysis levels, as P5 | level 1,
+//   P6 | level 2, P7 | coarse, P8 | level 2, the final synthesis alone: 256^2 97.9, 128^2 FP64
+//   83.4 (71.1 apart), since every pair waits for the longer of its two and the fused P6 + P7 has
+//   no place.
+// The pair kernels exist for 512 FFT cells per workgroup, and not for the all-bases tiling.  A
+// launch of more than kMaxPaired gridding chunks (eight to a CU; a large batch) fills the GPU from
+// either branch, and the two share it better on their own streams: 16 members of sides 64 to 256,
+// 3561 chunks, 31.3 ms paired, 30.8 apart.
+constexpr int kMaxPaired = 2048;
 inline bool paired(const PassLists& L, int mode) {
   if (L.cells != 512) return false;
   if (pm_tv(mode)) return true;
-  return mode != PM_INIT && L.sparse && L.vis == VisRoute::kFused && !(L.ana_wide & kAnaAllBases);
+  return mode != PM_INIT && L.sparse && L.vis == VisRoute::kFused && !(L.ana_wide & kAnaAllBases) &&
+         L.p7f.count <= kMaxPaired;
 }
 
 // How the iterations of `mode` run P6 and P7: fused where no SARA branch runs beside them (the

@@ -46,7 +46,7 @@ synthesis_final_kernel(const ProbDesc* __restrict__ descs, const int4* __restric
 }
 
 template <typename R>
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(kCoarseThreads)
 coarse_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items) {
   __shared__ CoarseSmem<R> sm;
   const int4 it = items[blockIdx.x];
@@ -55,16 +55,18 @@ coarse_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items
 
 template <typename R>
 int coarse_level(int n, int levels) {
-  // first level >= 2 whose input low-low band fits the LDS buffers
+  // first level >= 2 whose input low-low band fits; the largest only where it spares the branch
+  // its second analysis launch (sides up to twice that)
+  const int most = n <= 2 * CoarseMax<R>::value ? CoarseMax<R>::value : CoarseMax<R>::value / 2;
   for (int c = 2; c <= levels; ++c)
-    if ((n >> (c - 1)) <= CoarseMax<R>::value) return c;
+    if ((n >> (c - 1)) <= most) return c;
   return levels + 1;
 }
 
 template <typename R>
 void launch_coarse(const LaunchArgs& a) {
   if (a.nitems <= 0) return;
-  hipLaunchKernelGGL((coarse_kernel<R>), dim3(a.nitems), dim3(512), 0, a.stream, a.descs, a.items);
+  hipLaunchKernelGGL((coarse_kernel<R>), dim3(a.nitems), dim3(kCoarseThreads), 0, a.stream, a.descs, a.items);
 }
 
 template <typename R, int TOM>

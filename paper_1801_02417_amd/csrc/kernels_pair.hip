@@ -43,6 +43,7 @@ template <class A, class B>
 constexpr size_t max_size() { return sizeof(A) > sizeof(B) ? sizeof(A) : sizeof(B); }
 
 constexpr int kCells = 512;
+static_assert(kCoarseThreads == kGridThreads, "one workgroup size");
 
 // P5 with the first analysis level
 template <typename R, int TOM>

@@ -1,5 +1,5 @@
 """Iterations whose prior branch runs inside the data branch's launches: at most one analysis level
-before the coarse ones (sides up to 128 in FP32, 64 in FP64), for every tap count; against the
+before the coarse ones (sides up to 256 in FP32, 128 in FP64), for every tap count; against the
 oracle from a random state, to the bars of the iteration tests.  Batches of such sides, alone and
 mixed with a larger one, equal their members run alone, bitwise."""
 import numpy as np
@@ -30,7 +30,7 @@ def _solver(wl, b, prec, W=None):
 
 @pytest.mark.parametrize("prec,tol", [("fp64", 1e-10), ("fp32", 2e-6)])
 @pytest.mark.parametrize("n,M,taps,levels", [(8, 7, 4, 1), (16, 37, 6, 2), (32, 601, 8, 3), (64, 1511, 4, 1),
-                                             (64, 6000, 8, 4), (128, 3001, 6, 2)])
+                                             (64, 6000, 8, 4), (128, 3001, 6, 2), (256, 2001, 8, 3)])
 def test_paired_iterations(n, M, taps, levels, prec, tol):
     wl, b = _problem(n, M, taps, levels)
     W = np.random.default_rng(n).uniform(0.2, 1.0, size=(b.sara.J, 4))
@@ -50,7 +50,7 @@ def test_paired_iterations(n, M, taps, levels, prec, tol):
 
 
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
-@pytest.mark.parametrize("largest", [(64, 1511, 4), (256, 2001, 4)])
+@pytest.mark.parametrize("largest", [(64, 1511, 4), (256, 2001, 4), (512, 2001, 4)])
 def test_paired_batch_equals_alone(largest, prec):
     probs = [_problem(n, M, 8, lv) for n, M, lv in [(16, 37, 2), largest, (32, 601, 3)]]
     members = [_solver(wl, b, prec) for wl, b in probs]
