@@ -64,7 +64,6 @@ enum Scalar {
   SC_GFAC,          // factor of the last gridding pass, applied when its slots are summed
   SC_RES2,          // ||Y - phi(S)||^2
   SC_DOT,           // generic reduction results
-  SC_NRM2,
   SC_RV0, SC_RV1, SC_RV2, SC_RV3,      // ||X - S||^2 per Stokes
   SC_SN0, SC_SN1, SC_SN2, SC_SN3,      // ||2S - X||^2 per Stokes
   SC_RIMG2,         // sum of squares of the Stokes-I residual image
@@ -80,9 +79,11 @@ enum Scalar {
   SC_STOP_RV,       // bound of the largest relative variation of the four maps
   SC_STOP_NP,       // bound of N_p in percent (< 0: not used)
   SC_STOP_MAXIT,    // halt once SC_ITERS reaches it (0: no bound on the device)
-  NUM_SCALARS = 32
+  SC_LAM0 = 32,     // the last kNormRound Rayleigh quotients of the power iteration
+  NUM_SCALARS = 40
 };
-static_assert(SC_STOP_MAXIT < NUM_SCALARS, "scalar slots");
+constexpr int kNormRound = NUM_SCALARS - SC_LAM0;
+static_assert(SC_STOP_MAXIT < SC_LAM0, "scalar slots");
 // Partial sums per problem, each a (sum, compensation) pair of doubles: first the de-grid
 // region (n_p6 pairs), then kGenQ generic regions of gen_stride pairs each, then one pair per
 // gridding chunk for the fused de-grid + grid pass.

@@ -107,6 +107,9 @@ void launch_degrid_grid_t(int mode, const LaunchArgs& a, int src_slot, int out_s
   if (mode == GR_STOKES) {
     hipLaunchKernelGGL((degrid_grid_kernel<R, GR_STOKES, T>), grid, block, shm, a.stream, a.descs, a.items, src_slot,
                        out_slot, ce);
+  } else if (mode == GR_PLAIN) {
+    hipLaunchKernelGGL((degrid_grid_kernel<R, GR_PLAIN, T>), grid, block, shm, a.stream, a.descs, a.items, src_slot,
+                       out_slot, ce);
   } else {
     hipLaunchKernelGGL((degrid_grid_kernel<R, GR_DUAL, T>), grid, block, shm, a.stream, a.descs, a.items, src_slot,
                        out_slot, ce);
@@ -140,6 +143,7 @@ void set_degrid_limits_t(int max_ts) {
   hip_check(hipFuncSetAttribute((const void*)grid_kernel<R, GR_PLAIN, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   hip_check(hipFuncSetAttribute((const void*)grid_kernel<R, GR_STOKES, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   hip_check(hipFuncSetAttribute((const void*)degrid_grid_kernel<R, GR_DUAL, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
+  hip_check(hipFuncSetAttribute((const void*)degrid_grid_kernel<R, GR_PLAIN, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   hip_check(hipFuncSetAttribute((const void*)degrid_grid_kernel<R, GR_STOKES, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   hip_check(hipFuncSetAttribute((const void*)grid_mixed_kernel<R, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   const int W = max_ts + T - 1;

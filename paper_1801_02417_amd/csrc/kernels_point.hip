@@ -119,19 +119,26 @@ __global__ void __launch_bounds__(256) img_dot_kernel(const ProbDesc* __restrict
   if (threadIdx.x == 0) { double* g = gen_part(P, 1); g[2 * it.y] = t.s; g[2 * it.y + 1] = t.c; }
 }
 
-// dst = src / sqrt(scal[scalar])
+// dst = src / ||src||, ||src||^2 summed from img_dot_kernel's partials by every workgroup (in the
+// order finalize_kernel sums them), and scal[scalar] their dot product: one launch instead of two
+// sums and a scaling.
 template <typename R>
-__global__ void __launch_bounds__(256) img_scale_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int dst, int src, int scalar) {
+__global__ void __launch_bounds__(256) img_normalise_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int dst, int src, int scalar) {
+  __shared__ double red[8];
   const int4 it = items[blockIdx.x];
   const ProbDesc& P = descs[it.x];
   if (halted(P)) return;                 // stopped by an adaptive run
-  const int N = P.n * P.n, p = it.y * 256 + threadIdx.x;
-  if (p >= N) return;
-  const double nv = P.scal[scalar];
+  const int N = P.n * P.n, p = it.y * 256 + threadIdx.x, parts = (N + 255) / 256;
+  V4<R> v{};
+  if (p < N) v = ((const V4<R>*)P.img[src])[p];
+  const double nv = block_sum_partials(gen_part(P, 1), parts, red);
+  if (it.y == 0) {
+    const double d = block_sum_partials(gen_part(P, 0), parts, red);
+    if (threadIdx.x == 0) P.scal[scalar] = d;
+  }
   const R f = R(nv > 0.0 ? 1.0 / sqrt(nv) : 0.0);
-  V4<R> v = ((const V4<R>*)P.img[src])[p];
   v.x *= f; v.y *= f; v.z *= f; v.w *= f;
-  ((V4<R>*)P.img[dst])[p] = v;
+  if (p < N) ((V4<R>*)P.img[dst])[p] = v;
 }
 
 template <typename R>
@@ -238,8 +245,8 @@ template <typename R> void launch_npcount(const LaunchArgs& a) {
 template <typename R> void launch_img_dot(const LaunchArgs& a, int xs, int ys) {
   if (a.nitems > 0) hipLaunchKernelGGL((img_dot_kernel<R>), dim3(a.nitems), dim3(256), 0, a.stream, a.descs, a.items, xs, ys);
 }
-template <typename R> void launch_img_scale(const LaunchArgs& a, int dst, int src, int scalar) {
-  if (a.nitems > 0) hipLaunchKernelGGL((img_scale_kernel<R>), dim3(a.nitems), dim3(256), 0, a.stream, a.descs, a.items, dst, src, scalar);
+template <typename R> void launch_img_normalise(const LaunchArgs& a, int dst, int src, int scalar) {
+  if (a.nitems > 0) hipLaunchKernelGGL((img_normalise_kernel<R>), dim3(a.nitems), dim3(256), 0, a.stream, a.descs, a.items, dst, src, scalar);
 }
 template <typename R> void launch_fill(void* p, size_t count, hipStream_t s) {
   if (count == 0) return;
@@ -297,7 +304,7 @@ template <typename R> void launch_to_double(const void* src, double* dst, size_t
   template void launch_img_sumsq<R>(const LaunchArgs&, int, int, int);      \
   template void launch_npcount<R>(const LaunchArgs&);                       \
   template void launch_img_dot<R>(const LaunchArgs&, int, int);             \
-  template void launch_img_scale<R>(const LaunchArgs&, int, int, int);      \
+  template void launch_img_normalise<R>(const LaunchArgs&, int, int, int);  \
   template void launch_fill<R>(void*, size_t, hipStream_t);                 \
   template void launch_scale<R>(void*, size_t, double, hipStream_t);       \
   template void launch_gather_rows<R>(const double*, const int*, void*, long long, hipStream_t); \

@@ -45,8 +45,8 @@ template <typename R> void launch_fused_rows(int mode, const LaunchArgs& a, int 
 template <typename R> void launch_degrid(int mode, const LaunchArgs& a, int max_ts, int taps, int src_slot, int out_slot);
 template <typename R> void launch_grid(int mode, const LaunchArgs& a, int taps, int src_slot, int use_cfac);
 // P6 + P7 of an iteration in one pass over the gridding work list (mode GR_DUAL: de-grid with
-// the dual B step, then grid Bv; GR_STOKES: Algorithm 3's residual, then grid it); the column
-// inverse FFT after it takes factor mode 1 (GR_DUAL) or 2 (GR_STOKES)
+// the dual B step, then grid Bv; GR_STOKES: Algorithm 3's residual, then grid it; GR_PLAIN: grid
+// phi's rows, storing none); the column inverse FFT after it takes factor mode 1 (GR_DUAL) or 2
 template <typename R> void launch_degrid_grid(int mode, const LaunchArgs& a, int taps, int src_slot, int out_slot);
 // P7 (GR_DUAL) of the problems that run P6 and P7 as two passes and the fused pass of the others
 // (ProbDesc::fused_vis), in one launch
@@ -68,7 +68,9 @@ template <typename R> void launch_relvar(const LaunchArgs& a);
 template <typename R> void launch_img_sumsq(const LaunchArgs& a, int slot, int channel, int scalar);
 template <typename R> void launch_npcount(const LaunchArgs& a);
 template <typename R> void launch_img_dot(const LaunchArgs& a, int xs, int ys);
-template <typename R> void launch_img_scale(const LaunchArgs& a, int dst, int src, int scalar);
+// dst = src / ||src|| with ||src||^2 from launch_img_dot's partials (x, src), whose dot product
+// goes to scal[scalar]
+template <typename R> void launch_img_normalise(const LaunchArgs& a, int dst, int src, int scalar);
 template <typename R> void launch_fill(void* p, size_t count, hipStream_t s);
 // TV priors (items: {prob, block of 256 pixels, -, partial index}): the dual step of
 // Algorithm 3 on X, Psi A into IMG_PSIA, and the prior's value of IMG_S into region 0 partials

@@ -669,6 +669,7 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
                                                  unsigned long long* acc, unsigned char* stage_raw, double* red) {
   constexpr int RG = kGridTile + T - 1;             // acc: first the grid window (RG x RG cells)
   constexpr int DG = MODE == GR_STOKES ? DG_STOKES : DG_DUAL;
+  constexpr bool kStore = MODE != GR_PLAIN;         // GR_PLAIN: phi^dagger phi, the rows go nowhere else
   V2<R>* sf = (V2<R>*)stage_raw;
   V4<R>* su = (V4<R>*)(stage_raw + (size_t)ce * sizeof(V2<R>));
   static_assert(sizeof(Cell<R>) <= 8 * sizeof(unsigned long long), "window fits the accumulator");
@@ -718,8 +719,13 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
     kb_weights<R, T>(f.y, (const R*)P.kbpoly, w2);
     cplx<R> v[4];
     interpolate<R, T>(win, RG, (pk >> 16) - b1, (pk & 0xffff) - b2, w1, w2, v);
-    const Cell<R> o = degrid_row<R, DG>(P, m, v, src_slot, norm);
-    out[m] = o;
+    Cell<R> o;
+    if constexpr (kStore) {
+      o = degrid_row<R, DG>(P, m, v, src_slot, norm);
+      out[m] = o;
+    } else {
+      o = brightness<R>(P, m, v);
+    }
     sf[q] = f;
     V4<R> u0, u1;
     const R mx = grid_channels<R, MODE>(P, m, o, u0, u1);
@@ -727,13 +733,15 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
     su[2 * q + 1] = u1;
     bound.add((double)mx);
   }
-  const KSum nt = block_reduce(norm, red);                     // barriers: the window is done
-  if (threadIdx.x == 0) {
-    double* pp = chunk_partials(P);
-    pp[2 * ch.w] = nt.s;
-    pp[2 * ch.w + 1] = nt.c;
+  if constexpr (kStore) {
+    const KSum nt = block_reduce(norm, red);
+    if (threadIdx.x == 0) {
+      double* pp = chunk_partials(P);
+      pp[2 * ch.w] = nt.s;
+      pp[2 * ch.w + 1] = nt.c;
+    }
   }
-  const double total = block_reduce(bound, red).value();
+  const double total = block_reduce(bound, red).value();       // barriers: the window is done
   for (int q = threadIdx.x; q < 8 * RG * RG; q += blockDim.x) acc[q] = 0ull;
   __syncthreads();
   grid_chunk<R, T, false>(P, ch, sf, su, acc, fixed_exponent<R>(total), pre);
