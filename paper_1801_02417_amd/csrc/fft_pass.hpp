@@ -235,9 +235,38 @@ __device__ __forceinline__ void fft_pass(const ProbDesc& P, const int4 it, int s
     // factor c = rho2 max(0, 1 - epsilon / ||Bv||) from the fused pass's per-chunk partials,
     // reduced by every workgroup in the same fixed order and stored, with ||Bv||^2, by the
     // problem's first; 2 one; 3 the first or the second, as the problem's route is)
+    // The sum shares the staging's barrier: its wave totals go to LDS with the tables, and the
+    // factor is worked out while the gathers are in flight.
     if (src_slot == 3) src_slot = P.fused_vis;
+    const int ntg = P.ntile_side_g;
+    trow0 = line0 / kGridTile - 1;
+    const int ntr = min(K - 1, line0 + lines - 1) / kGridTile - trow0 + 1;
+    const double* __restrict__ parts = chunk_partials(P);
+    const int nparts = src_slot == 1 ? P.n_slots : 0;
+    auto tile_at = [&](int i) { return (i & (ntg - 1)) * ntg + ((trow0 + (i >> lg2(ntg)) + ntg) & (ntg - 1)); };
+    int2 sl0 = make_int2(0, 0);
+    int bx0 = 0;
+    if (threadIdx.x < ntr * ntg) {
+      sl0 = P.tile_slots[tile_at(threadIdx.x)];
+      bx0 = P.tile_box[tile_at(threadIdx.x)];
+    }
     if (src_slot == 1) {
-      const double v2 = block_sum_partials(chunk_partials(P), P.n_slots, red);
+      KSum k;
+      for (int i = threadIdx.x; i < nparts; i += nthr) {
+        KSum o; o.s = parts[2 * i]; o.c = parts[2 * i + 1]; k.merge(o);
+      }
+      k = wave_reduce(k);
+      if ((threadIdx.x & 63) == 0) { red[2 * (threadIdx.x >> 6)] = k.s; red[2 * (threadIdx.x >> 6) + 1] = k.c; }
+    }
+    for (int i = threadIdx.x; i < ntr * ntg; i += nthr) {
+      tsl[i] = i == threadIdx.x ? sl0 : P.tile_slots[tile_at(i)];
+      tbx[i] = i == threadIdx.x ? bx0 : P.tile_box[tile_at(i)];
+    }
+    __syncthreads();
+    if (src_slot == 1) {
+      KSum t;
+      for (int w = 0; w < (nthr + 63) >> 6; ++w) { KSum o; o.s = red[2 * w]; o.c = red[2 * w + 1]; t.merge(o); }
+      const double v2 = t.value();
       const double vn = sqrt(v2);
       const double c = (vn > P.eps) ? P.rho2 * (1.0 - P.eps / vn) : 0.0;
       if (line0 == 0 && threadIdx.x == 0) {
@@ -249,18 +278,6 @@ __device__ __forceinline__ void fft_pass(const ProbDesc& P, const int4 it, int s
     } else if (src_slot == 0) {
       gfac = R(P.scal[SC_GFAC]);
     }
-    const int ntg = P.ntile_side_g;
-    trow0 = line0 / kGridTile - 1;
-    const int ntr = min(K - 1, line0 + lines - 1) / kGridTile - trow0 + 1;
-    for (int i = threadIdx.x; i < ntr * ntg; i += nthr) {
-      const int rr = i >> lg2(ntg), u1 = i & (ntg - 1);
-      const int t = u1 * ntg + ((trow0 + rr + ntg) & (ntg - 1));
-      const int2 sl = P.tile_slots[t];
-      const int bx = P.tile_box[t];
-      tsl[i] = sl;
-      tbx[i] = bx;
-    }
-    __syncthreads();
   }
   // P9 + P1 + P4: the primal step's inputs of the thread's pixel are requested now, so their loads
   // overlap the loads and the inverse FFT below (not by FP64's 1024 threads, whose 128 registers
