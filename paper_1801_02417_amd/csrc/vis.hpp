@@ -492,6 +492,27 @@ __device__ inline void grid_chunk(const ProbDesc& P, const int4 ch,
   }
 }
 
+// The taps of one row shared by the lanes of a group of eight: this lane's tap row (its eight
+// cells at row, its weight w2, 0 for lanes beyond T), and the sum over the group to every lane.
+template <typename R, int T>
+__device__ inline void interpolate_row(const Cell<R>* row, const R* w1, R w2, cplx<R> v[4]) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) v[s] = cmk(R(0), R(0));
+#pragma unroll
+  for (int i = 0; i < T; ++i) {
+    const Cell<R> c = row[i];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) { v[s].re += w1[i] * c.s[s].re; v[s].im += w1[i] * c.s[s].im; }
+  }
+  auto group_sum = [](R x) {
+    x += dpp_move<0xB1>(x);                        // lane ^ 1
+    x += dpp_move<0x4E>(x);                        // lane ^ 2
+    return x + half_mirror(x);                     // the other quad
+  };
+#pragma unroll
+  for (int s = 0; s < 4; ++s) v[s] = cmk(group_sum(v[s].re * w2), group_sum(v[s].im * w2));
+}
+
 // A value of lane e (e the same in every lane), read into a scalar register.
 template <typename V>
 __device__ inline V lane_value(V v, int e) {
@@ -664,6 +685,14 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
 // staged in LDS (in the memory the accumulation takes afterwards); each row is de-gridded there
 // by one thread, stored (Bv, or the residual) and staged for the gridding of the same chunk,
 // and the FP64 squared norms of the chunk go to its pair of chunk_partials.
+//
+// One thread per row leaves most of the workgroup idle in a chunk of few rows, and the row's T x T
+// taps a chain of their own: there a group of eight lanes shares a row, a tap row to a lane, as
+// long as one pass of the groups covers the chunk.  us per iteration, a thread to a row -> this:
+// 64^2 34.4 -> 33.0, initialisation of 256^2 / 2e5 65.5 -> 64.0 and of 512^2 / 1e6 206 -> 200, TV at
+// 256^2 65.2 -> 63.7; with two passes (128 rows) 128^2 with Mueller matrices lost 1.5 %.  Not in
+// FP64, where the lanes' polynomials cost registers that spill (32^2 39.0 -> 41.1).
+constexpr int kFewRows = kGridThreads / 8;
 template <typename R, int MODE, int T>
 __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 it, int src_slot, int out_slot, int ce,
                                                  unsigned long long* acc, unsigned char* stage_raw, double* red) {
@@ -688,9 +717,12 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
   const V2<R>* __restrict__ frac = (const V2<R>*)P.vis_frac;
   int me[2], pke[2];
   V2<R> fe[2];
+  // (few rows: eight lanes to a row, see below)
+  const bool few = sizeof(R) == 4 && ne <= kFewRows;
+  const int q0 = few ? threadIdx.x >> 3 : threadIdx.x, qs = few ? kGridThreads / 8 : kGridThreads;
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const int q = threadIdx.x + e * blockDim.x;
+    const int q = q0 + e * qs;
     me[e] = ent.x + (q < ne ? q : 0);                      // the chunk's rows are contiguous
   }
 #pragma unroll
@@ -710,15 +742,25 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
   KSum bound, norm;
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const int q = threadIdx.x + e * blockDim.x;
+    const int q = q0 + e * qs;
     if (q >= ne) break;
     const int m = me[e], pk = pke[e];
     const V2<R> f = fe[e];
-    R w1[T], w2[T];
+    R w1[T];
     kb_weights<R, T>(f.x, (const R*)P.kbpoly, w1);
-    kb_weights<R, T>(f.y, (const R*)P.kbpoly, w2);
     cplx<R> v[4];
-    interpolate<R, T>(win, RG, (pk >> 16) - b1, (pk & 0xffff) - b2, w1, w2, v);
+    if (few) {
+      R cr[KbDeg<R>::value + 1];
+      load_poly<R, T>(P, cr);                              // lane i takes tap row i
+      const int lane8 = threadIdx.x & 7, j = lane8 < T ? lane8 : 0;
+      const R w2 = kb_tap<R, T>(R(2) * f.y - R(T - 1), cr);
+      interpolate_row<R, T>(win + ((pk & 0xffff) - b2 + j) * RG + (pk >> 16) - b1, w1, w2, v);
+      if (lane8 != 0) continue;
+    } else {
+      R w2[T];
+      kb_weights<R, T>(f.y, (const R*)P.kbpoly, w2);
+      interpolate<R, T>(win, RG, (pk >> 16) - b1, (pk & 0xffff) - b2, w1, w2, v);
+    }
     Cell<R> o;
     if constexpr (kStore) {
       o = degrid_row<R, DG>(P, m, v, src_slot, norm);
