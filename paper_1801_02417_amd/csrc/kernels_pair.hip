@@ -17,8 +17,6 @@
 
 namespace psara {
 
-namespace {
-
 struct Pair {
   const ProbDesc* descs;
   const int4* a;      // data branch items
@@ -112,7 +110,7 @@ __global__ void __launch_bounds__(256) p8_tv_synth_kernel(Pair q) {
   else tv_synth_item<R>(q.descs[it.x], it);
 }
 
-Pair make_pair(const LaunchArgs& a, const LaunchArgs& b, bool b_first, dim3& grid) {
+static Pair make_pair(const LaunchArgs& a, const LaunchArgs& b, bool b_first, dim3& grid) {
   const int head = b_first ? b.nitems : a.nitems, tail = b_first ? a.nitems : b.nitems;
   const int lead = (head + 7) / 8 * 8;
   grid = dim3(lead + tail);
@@ -132,8 +130,6 @@ void launch_grid_coarse_t(const LaunchArgs& a, const LaunchArgs& b) {
   const size_t lds = grid_coarse_lds<R, T>(a.grid_ce);
   hipLaunchKernelGGL((grid_coarse_kernel<R, T>), grid, dim3(kGridThreads), lds, a.stream, q, a.grid_ce);
 }
-
-}  // namespace
 
 template <typename R>
 void launch_p5_analysis(const LaunchArgs& a, const LaunchArgs& b) {

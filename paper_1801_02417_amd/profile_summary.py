@@ -31,14 +31,14 @@ COPY_BYTES = 256 << 20          # bench.py --calibrate-copy moves 64 Mi floats e
 
 # pass id (as in psara_profile_passes) -> (kernel name prefix, source file)
 PASS_KERNELS = {
-    0: ("void psara::fft_pass_kernel<float, 512, 0, 0>", "kernels_fft.hip"),
-    4: ("void psara::fft_pass_kernel<float, 512, 1, -1>", "kernels_fft.hip"),
-    5: ("void psara::degrid_kernel<float, 0, 8>", "kernels_grid.hip"),
-    6: ("void psara::grid_kernel<float, 0, 8>", "kernels_grid.hip"),
-    7: ("void psara::fft_pass_kernel<float, 512, 2, -1>", "kernels_fft.hip"),
-    8: ("void psara::fft_pass_kernel<float, 512, 3, -1>", "kernels_fft.hip"),
-    9: ("void psara::fft_pass_kernel<float, 512, 4, 0>", "kernels_fft.hip"),
-    10: ("void psara::degrid_grid_kernel<float, 0, 8>", "kernels_grid.hip"),
+    0: ("void psara::fft_pass_kernel<float, 512, 0, 0>", "fft_pass.hpp"),
+    4: ("void psara::fft_pass_kernel<float, 512, 1, -1>", "fft_pass.hpp"),
+    5: ("void psara::degrid_kernel<float, 0, 8>", "vis.hpp"),
+    6: ("void psara::grid_kernel<float, 0, 8>", "vis.hpp"),
+    7: ("void psara::fft_pass_kernel<float, 512, 2, -1>", "fft_pass.hpp"),
+    8: ("void psara::fft_pass_kernel<float, 512, 3, -1>", "fft_pass.hpp"),
+    9: ("void psara::fft_pass_kernel<float, 512, 4, 0>", "fft_pass.hpp"),
+    10: ("void psara::degrid_grid_kernel<float, 0, 8>", "vis.hpp"),
 }
 
 
