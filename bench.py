@@ -37,7 +37,7 @@ PASS_SOURCES = ["fft_pass.hpp", "dwt.hpp", "dwt.hpp", "fft_pass.hpp", "fft_pass.
                 "vis.hpp", "vis.hpp", "fft_pass.hpp", "fft_pass.hpp", "fft_pass.hpp",
                 "vis.hpp"]
 PASS_KERNELS = ["fft_pass_kernel<float,512,0,0>", "analysis_kernel+coarse_kernel+synthesis_kernel+synthesis_final_kernel",
-                "-", "-", "fft_pass_kernel<float,512,1,-1>", "degrid_kernel<float,0,8>", "grid_kernel<float,0,8>",
+                "-", "-", "fft_pass_kernel<float,512,1,-1>", "degrid_kernel<float,0,8>", "grid_kernel<float,1,8>",
                 "fft_pass_kernel<float,512,2,-1>", "fft_pass_kernel<float,512,3,-1>", "fft_pass_kernel<float,512,4,0>",
                 "degrid_grid_kernel<float,0,8>"]
 # the single-launch passes a constrained iteration runs (the chain's first P1+P4 and last P9

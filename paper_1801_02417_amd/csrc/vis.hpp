@@ -11,7 +11,7 @@
 // their own with plain stores; the column inverse FFT sums the slots covering each cell in a
 // fixed order, so no global atomics are used.  Both also exist as one fused pass over the
 // gridding chunks (a chunk's taps all lie in the region it accumulates), which the iterations
-// use when no other branch runs beside them.
+// use unless a SARA branch runs on a stream beside them.
 //
 // The dual variable B is kept as B = c * Bv: the de-gridding pass writes
 // Bv = B/rho2 + phi(X) - Y and the FP64 partial sums of ||Bv||^2; the gridding pass reduces
@@ -683,7 +683,7 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
 // A chunk's rows all have their window start in its tile, so every tap they read lies in the
 // tile plus its (T-1)-wide halo -- the region the chunk accumulates.  The region of the grid is
 // staged in LDS (in the memory the accumulation takes afterwards); each row is de-gridded there
-// by one thread, stored (Bv, or the residual) and staged for the gridding of the same chunk,
+// by one thread, or by eight (below), stored (Bv, or the residual) and staged for the gridding of the same chunk,
 // and the FP64 squared norms of the chunk go to its pair of chunk_partials.
 //
 // One thread per row leaves most of the workgroup idle in a chunk of few rows, and the row's T x T

@@ -34,7 +34,7 @@ PASS_KERNELS = {
     0: ("void psara::fft_pass_kernel<float, 512, 0, 0>", "fft_pass.hpp"),
     4: ("void psara::fft_pass_kernel<float, 512, 1, -1>", "fft_pass.hpp"),
     5: ("void psara::degrid_kernel<float, 0, 8>", "vis.hpp"),
-    6: ("void psara::grid_kernel<float, 0, 8>", "vis.hpp"),
+    6: ("void psara::grid_kernel<float, 1, 8>", "vis.hpp"),
     7: ("void psara::fft_pass_kernel<float, 512, 2, -1>", "fft_pass.hpp"),
     8: ("void psara::fft_pass_kernel<float, 512, 3, -1>", "fft_pass.hpp"),
     9: ("void psara::fft_pass_kernel<float, 512, 4, 0>", "fft_pass.hpp"),
