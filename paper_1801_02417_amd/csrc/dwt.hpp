@@ -590,8 +590,8 @@ __device__ __forceinline__ void coarse_body(const ProbDesc& P, int w, int ch, in
   constexpr int s = CoarseMax<R>::value + 1;
   // the low-low band in rounds of NB loads; the duals and thresholds of the coarse bands (the
   // top-left m0 x m0 block of the basis) in rounds of NB, a round ahead of the updates that use
-  // them, the first one ahead of the filters
-  constexpr int NB = 8;
+  // them, the first one ahead of the filters (FP64: four at a time, for the registers)
+  constexpr int NB = sizeof(R) == 8 ? 4 : 8;
   for (int q0 = threadIdx.x; q0 < m0 * m0; q0 += NB * kCoarseThreads) {
     R v[NB];
 #pragma unroll
