@@ -18,6 +18,7 @@ constexpr int kMaxCheb = 17;     // Chebyshev coefficients per tap (degree <= 16
 constexpr int kMaxLevels = 8;
 constexpr int kRunMax = 32;         // longest run of same-window visibilities one lane group takes
 constexpr int kChunkEntries = 1024; // largest gridding chunk (entries per workgroup, staged in LDS)
+constexpr int kLeastChunk = 64;     // smallest chunk size
 constexpr int kGridThreads = 512;   // threads per gridding workgroup (64 lane groups of 8)
 constexpr int kSmallChunk = 16;     // a chunk of at most this many entries is gridded by one wave
 constexpr int kGridFactorItem = -1;  // gridding work item that stores the pass's factor
@@ -119,7 +120,8 @@ static_assert(sizeof(GlobalPtr<void>) == sizeof(void*), "one layout on the host 
 // Per-problem descriptor.  Pointers are typed by the engine's real type R.
 struct ProbDesc {
   int n, K, T, levels;
-  int fused_vis;         // P6 and P7 of the iterations beside a SARA branch run as the fused pass
+  int chunk_norm;        // ||Bv||^2 of the iterations is summed by gridding chunk (either route of
+                         // P6 and P7 may run), not by de-grid item
   int nbases, has_dirac, nwav, ts;      // ts = grid tile side
   int ntile_side, deg, n_p6, gen_stride;
   int ntile_side_g;       // gridding tiles per side (side kGridTile)
@@ -221,6 +223,13 @@ template <typename R> __host__ __device__ inline cplx<R> cmul(cplx<R> a, cplx<R>
 template <typename R> __host__ __device__ inline cplx<R> cscale(cplx<R> a, R s) { return cmk(a.re * s, a.im * s); }
 template <typename R> __host__ __device__ inline cplx<R> cmuli(cplx<R> a) { return cmk(-a.im, a.re); }   // i * a
 template <typename R> __host__ __device__ inline cplx<R> cconj(cplx<R> a) { return cmk(a.re, -a.im); }
+
+// a product that is rounded on its own (never contracted into a following add)
+template <typename R>
+__host__ __device__ __forceinline__ R mul_rn(R a, R b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
 
 // --------------------------------------------------------------------------------------------
 // compensated FP64 sums (Neumaier), combinable in a fixed tree

@@ -210,13 +210,14 @@ void check_tuning(const Tuning& t, int K) {
     throw Error(PSARA_EINVAL, "fft_cells must be 0 or 512, 1024 or 2048, and at least the grid side 2n");
 }
 
-// Whether a problem's iterations beside a SARA branch run P6 and P7 as one fused pass.  Alone the
-// fused pass is the faster, but its large workgroups share the CUs badly with SARA kernels on
-// another stream (256^2 there: 5 % slower than the two passes); as one of the paired launches, which a
-// branch with at most one analysis level before the coarse ones takes, it stays the faster.  By
-// the problem and not by the launch, so that a member of a batch, whose launches may be another's,
-// computes what it computes alone.
-static bool fused_vis(int levels, int c_level) { return levels < 2 || c_level <= 2; }
+// Whether ||Bv||^2 of a problem's iterations is summed by gridding chunk (ProbDesc::chunk_norm),
+// so that a launch may run P6 and P7 as one fused pass or as two: where the branch of the prior
+// can run in the data branch's launches (paired() below), with at most one analysis level before
+// the coarse ones and a grid side that the pair kernels take.  The larger problems run two passes
+// in every launch: beside a SARA branch on another stream the fused pass's workgroups share the
+// CUs worse (us per iteration, fused -> two passes: 512^2 / 1e6 rows 282 -> 269, with one wavelet level
+// 258 -> 246, 1024^2 / 1e6 with one level 743 -> 640, 512^2 / 3e5 FP64 with one level 427 -> 382).
+static bool chunk_norm(int K, int levels, int c_level) { return K <= 512 && (levels < 2 || c_level <= 2); }
 
 // ------------------------------------------------------------------------------------------------
 // work lists (appended per problem, so batches concatenate them)
@@ -635,7 +636,8 @@ void Engine<R>::upload_items() {
   pl_.grid_ce = geo_.chunk_entries;
   pl_.sparse = h_.coef[COEF_A] != nullptr && h_.nwav > 0;
   pl_.tv = h_.tv_kind != 0;
-  pl_.vis = h_.fused_vis ? VisRoute::kFused : VisRoute::kSplit;
+  pl_.chunk_norm = h_.chunk_norm != 0;
+  pl_.vis = geo_.M;
 }
 
 template <typename R>
@@ -775,7 +777,7 @@ void Engine<R>::set_prior(uint32_t mask, int levels, const double* weights, doub
   copy_sync(h_.coef[COEF_GW], gw.data(), gw.size() * sizeof(R), hipMemcpyHostToDevice, s0_, "weights upload");
   zero(h_.coef[COEF_A], coef_elems_ * sizeof(V4<R>));
   c_level_ = coarse_level<R>(n, levels);
-  h_.fused_vis = fused_vis(levels, c_level_) ? 1 : 0;
+  h_.chunk_norm = chunk_norm(geo_.K, levels, c_level_) ? 1 : 0;
   build_prior_items();
   realloc_partials();
   upload_items();
@@ -839,56 +841,69 @@ void launch_sara_dual(const PassLists& L, hipStream_t s) {
 
 // Whether the prior's branch runs inside the data branch's launches (kernels_pair.hip) rather
 // than on a stream of its own: where it has no more stages than the data branch has passes
-// between the row passes (every problem's SARA branch by fused_vis(), and the TV priors).
+// between the row passes (every problem's SARA branch by chunk_norm(), and the TV priors).
 //   us per iteration, apart -> paired: 32^2 FP64 50.4 -> 46.6, 64^2 41.9 -> 37.6, 128^2 51.5 ->
 //   47.9, 256^2 94.3 -> 84.8, TV at 256^2 76.0 -> 65.7.  With two analysis levels, as P5 | level 1,
 //   P6 | level 2, P7 | coarse, P8 | level 2, the final synthesis alone: 256^2 97.9, 128^2 FP64
 //   83.4 (71.1 apart), since every pair waits for the longer of its two and the fused P6 + P7 has
 //   no place.
 // The pair kernels exist for 512 FFT cells per workgroup, and not for the all-bases tiling.  A
-// launch of more than kMaxPaired gridding chunks (eight to a CU; a large batch) fills the GPU from
-// either branch, and the two share it better on their own streams: 16 members of sides 64 to 256,
-// 3561 chunks, 31.3 ms paired, 30.8 apart.
-constexpr int kMaxPaired = 2048;
-inline bool paired(const PassLists& L, int mode) {
+// launch of more than kMaxPaired gridding chunks (a large batch, or very many rows) fills the GPU from
+// either branch, and the two share it better on their own streams; FP64 has one gridding
+// workgroup to a CU, FP32 up to four.
+//   us per iteration, chunks: paired / apart
+//   FP32  128^2, 1.2e4 rows  720: 68 / 75   1440: 112 / 114  2160: 159 / 154  2880: 209 / 195
+//         256^2, 2e5         848: 85 / 93   1696: 132 / 137  2544: 185 / 182  3392: 250 / 238
+//         64^2, 1511         816: 73 / 77   1632: 125 / 122  3264: 238 / 208
+//         128^2, 4e4         932: 80 / 90   1864: 132 / 143  3728: 256 / 244
+//   FP64  128^2, 1.2e4       180: 65 / 71   360: 83 / 80     720: 132 / 120   1440: 241 / 193
+//         32^2, 600          152: 51 / 55   304: 69 / 66     608: 105 / 93
+//         64^2, 3000         184: 67 / 74   368: 90 / 90     736: 158 / 137
+template <typename R> constexpr int kMaxPaired = sizeof(R) == 4 ? 2048 : 256;
+template <typename R>
+bool paired(const PassLists& L, int mode) {
   if (L.cells != 512) return false;
   if (pm_tv(mode)) return true;
-  return mode != PM_INIT && L.sparse && L.vis == VisRoute::kFused && !(L.ana_wide & kAnaAllBases) &&
-         L.p7f.count <= kMaxPaired;
+  return mode != PM_INIT && L.sparse && L.chunk_norm && !(L.ana_wide & kAnaAllBases) &&
+         L.p7f.count <= kMaxPaired<R>;
 }
 
-// How the iterations of `mode` run P6 and P7: fused where no SARA branch runs beside them (the
-// initialisation stage, Algorithm 3), else as each problem's fused_vis says
-inline VisRoute vis_route(const PassLists& L, int mode) {
-  return pm_tv(mode) || mode == PM_INIT || !L.sparse ? VisRoute::kFused : L.vis;
+// Whether the iterations of `mode` run P6 and P7 as the fused pass: where no SARA branch runs on
+// another stream (the initialisation stage, Algorithm 3, the paired launches), and beside one
+// where the chunks hold kFullChunk rows on average, since the fused pass stages and clears a
+// chunk's region whatever it holds.
+//   us per iteration beside a SARA branch, rows in a chunk: two passes / fused
+//   FP32  66: 371 / 397   172: 467 / 484   236: 249 / 238   367: 331 / 328   998: 599 / 571
+//   FP64  66: 798 / 902   172: 526 / 542   367: 407 / 377   400: 465 / 443   944: 766 / 584
+// Also with kFewChunks chunks or fewer (a launch that only its FFT cells keep from being paired): they
+// leave CUs idle, and one launch takes less than two.  1024 or 2048 cells, chunks: FP32 51: 58 / 52, 180:
+// 55 / 58; FP64 180: 82 / 72.
+constexpr long long kFullChunk = 200;
+template <typename R> constexpr int kFewChunks = sizeof(R) == 4 ? 128 : 256;
+template <typename R>
+bool fused_vis(const PassLists& L, int mode) {
+  if (pm_tv(mode) || mode == PM_INIT || !L.sparse || paired<R>(L, mode)) return true;
+  return L.chunk_norm && (L.vis >= kFullChunk * L.p7f.count || L.p7f.count <= kFewChunks<R>);
 }
 
 // P6, P7 and P8 of one iteration (the dual B step or Algorithm 3's residual, its gridding, and
-// the column inverse FFT, which takes the factor of the gridded values from the partials of the
-// fused pass, as one for the TV residual, or as the grid pass stored it)
+// the column inverse FFT, which takes the factor of the gridded values from the per-chunk
+// partials, as one for the TV residual, or as the grid pass stored it)
 template <typename R>
 void launch_p6_p7(const PassLists& L, int mode, hipStream_t s) {
   if (pm_tv(mode)) {
     launch_degrid_grid<R>(GR_STOKES, lists_la(L, L.p7f, s), L.taps, VIS_Y, VIS_R);
-    return;
-  }
-  const VisRoute v = vis_route(L, mode);
-  if (v == VisRoute::kFused) {
+  } else if (fused_vis<R>(L, mode)) {
     launch_degrid_grid<R>(GR_DUAL, lists_la(L, L.p7f, s), L.taps, VIS_BV, VIS_BV);
-  } else if (v == VisRoute::kSplit) {
+  } else {
     launch_degrid<R>(DG_DUAL, lists_la(L, L.p6, s), L.max_ts, L.taps, VIS_BV, VIS_BV);
     launch_grid<R>(GR_DUAL, lists_la(L, L.p7, s), L.taps, VIS_BV, 0);
-  } else {
-    launch_degrid<R>(DG_DUAL, lists_la(L, L.p6s, s), L.max_ts, L.taps, VIS_BV, VIS_BV);
-    launch_grid_mixed<R>(lists_la(L, L.p7m, s), L.taps);
   }
 }
 
 template <typename R>
 void launch_p8(const PassLists& L, int mode, hipStream_t s) {
-  const VisRoute v = vis_route(L, mode);
-  const int factor = pm_tv(mode) ? 2 : v == VisRoute::kMixed ? 3 : v == VisRoute::kFused ? 1 : 0;
-  launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, factor, 0);
+  launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, pm_tv(mode) ? 2 : fused_vis<R>(L, mode) ? 1 : 3, 0);
 }
 
 // The passes of one iteration between the row passes, the prior's stages beside them
@@ -917,7 +932,7 @@ void launch_iterations(const PassLists& L, int mode, int count, hipStream_t s0, 
   // transforms S_new): residual Phi S - Y L^{-1} per Stokes map, gridded without mixing
   const bool tvm = pm_tv(mode);
   const bool sparse = tvm || ((mode != PM_INIT) && L.sparse);
-  const bool pair = sparse && paired(L, mode);
+  const bool pair = sparse && paired<R>(L, mode);
   for (int k = 0; k < count; ++k) {
     if (pair) {
       launch_paired<R>(L, mode, s0);
@@ -1490,22 +1505,16 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
   for (int i = 0; i <= NP; ++i) hip_check(hipEventCreate(&ev[i]), "event");
   for (int i = 0; i <= NP + 1; ++i) ms[i] = 0.0;
   const bool sparse = (mode != PM_INIT) && L.sparse;
-  // P5 .. P8 with P6 and P7 timed as two passes; where the iterations run them fused, the two work
-  // on copies (VIS_R is scratch, the plain gridding leaves the l2-ball factor alone), and the passes
-  // that count follow untimed, so the state advances as the iterations advance it
-  const VisRoute route = vis_route(L, mode);
-  const bool fused = route == VisRoute::kFused;
+  const bool fused = fused_vis<R>(L, mode);
+  // P5 .. P8 with P6 and P7 as two passes (where the iterations fuse them, with the same bits)
   auto p5_p8 = [&]() {
     launch_fft<R>(1, lists_la(L, L.cols, s), L.cells, 0, 0);
     hip_check(hipEventRecord(ev[5], s), "event record");
-    const bool split = route == VisRoute::kSplit;
-    launch_degrid<R>(DG_DUAL, lists_la(L, L.p6, s), L.max_ts, L.taps, VIS_BV, split ? VIS_BV : VIS_R);
+    launch_degrid<R>(DG_DUAL, lists_la(L, L.p6, s), L.max_ts, L.taps, VIS_BV, VIS_BV);
     hip_check(hipEventRecord(ev[6], s), "event record");
-    launch_grid<R>(split ? GR_DUAL : GR_PLAIN, lists_la(L, L.p7, s), L.taps, split ? VIS_BV : VIS_R, 0);
+    launch_grid<R>(GR_DUAL, lists_la(L, L.p7, s), L.taps, VIS_BV, 0);
     hip_check(hipEventRecord(ev[7], s), "event record");
-    if (!split) launch_p6_p7<R>(L, mode, s);
-    hip_check(hipEventRecord(ev[3], s), "event record");
-    launch_p8<R>(L, mode, s);
+    launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, 3, 0);
     hip_check(hipEventRecord(ev[8], s), "event record");
   };
   // P5 .. P8 as the iterations run them, with the fused P6 + P7 pass timed where they use it
@@ -1529,7 +1538,7 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
     for (int i = 0; i < NP; ++i) {
       if (i == 2 || i == 3) continue;          // P3 runs inside P2's launches, P4 inside P1's
       float t = 0.f;
-      hip_check(hipEventElapsedTime(&t, ev[i == 4 ? 2 : i == 7 ? 3 : i], ev[i + 1]), "elapsed");
+      hip_check(hipEventElapsedTime(&t, ev[i == 4 ? 2 : i], ev[i + 1]), "elapsed");
       ms[i] += t;
     }
   }
@@ -1638,24 +1647,10 @@ Batch<R>::Batch(const std::vector<Engine<R>*>& members, hipStream_t stream) : me
   pl_.ana_wide = ana_wide;
   pl_.grid_ce = grid_ce;
   pl_.sparse = sparse;
-  // the members whose main iterations run P6 and P7 fused, and the others
-  auto part = [&](const std::vector<int4>& v, int fused) {
-    std::vector<int4> o;
-    for (const int4& it : v)
-      if (members_[it.x]->desc().fused_vis == fused) o.push_back(it);
-    return o;
-  };
-  size_t fused = 0;
-  for (Engine<R>* e : members_) fused += e->desc().fused_vis != 0;
-  pl_.vis = fused == members_.size() ? VisRoute::kFused : fused ? VisRoute::kMixed : VisRoute::kSplit;
-  if (pl_.vis == VisRoute::kMixed) {
-    std::vector<int4> p6s = part(S.p6, 0);
-    order_degrid_items(p6s.begin(), p6s.end());
-    std::vector<int4> p7m = part(S.p7, 0);
-    for (const int4& it : part(S.p7f, 1))
-      if (it.y >= 0) p7m.push_back(it);
-    order_grid_items(p7m.begin(), p7m.end(), [this](int prob) { return &members_[prob]->geometry(); });
-    up(pl_.p6s, p6s); up(pl_.p7m, p7m);
+  pl_.chunk_norm = true;
+  for (Engine<R>* e : members_) {
+    pl_.chunk_norm = pl_.chunk_norm && e->desc().chunk_norm != 0;
+    pl_.vis += e->geometry().M;
   }
   set_grid_kernel_limits<R>(max_ts, T);
   set_pair_kernel_limits<R>();

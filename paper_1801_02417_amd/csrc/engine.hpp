@@ -82,19 +82,17 @@ struct DevItems {
 
 // The device work lists and launch shapes of one set of problems (one solve, or a batch of
 // solves that share a precision and a tap count) that the iteration's pass sequence runs on.
-// How P6 and P7 run: as two passes, as one, or either by the problem (ProbDesc::fused_vis)
-enum class VisRoute { kSplit, kFused, kMixed };
 struct PassLists {
   const ProbDesc* descs = nullptr;
   DevItems img, rows, cols, p6, p7, p7f, synfinal, coarse;
-  DevItems p6s, p7m;               // VisRoute::kMixed: P6 of the split problems; P7 of them, the fused pass of the others
   DevItems ana_d[kMaxLevels + 1], syn_d[kMaxLevels + 1];
   int cells = 512, rcells = 512;   // FFT cells per workgroup of the column / row passes
   int max_ts = 16, taps = 8, max_levels = 0;
   int max_n = 0;                   // largest image side among the problems
   int ana_wide = 1;                // the problems' analysis tilings (kAnaWide | kAnaAllBases bits)
   int grid_ce = kChunkEntries;     // largest gridding chunk among the problems
-  VisRoute vis = VisRoute::kSplit; // the route beside a SARA branch
+  bool chunk_norm = false;         // every problem has ProbDesc::chunk_norm
+  long long vis = 0;               // visibilities of all problems
   bool sparse = false;             // every problem has a wavelet prior (P2/P3 run)
   bool tv = false;                 // the problems carry a TV prior (Algorithm 3)
 };

@@ -167,13 +167,6 @@ __device__ __forceinline__ void quad_transpose(R* a) {
   }
 }
 
-// a product that is rounded on its own (never contracted into a following add)
-template <typename R>
-__device__ __forceinline__ R mul_rn(R a, R b) {
-#pragma clang fp contract(off)
-  return a * b;
-}
-
 template <typename R>
 __device__ inline Cell<R> zero_cell() {
   Cell<R> c;
@@ -232,12 +225,12 @@ __device__ __forceinline__ void fft_pass(const ProbDesc& P, const int4 it, int s
   R gfac = R(1);
   if (PASS == 2) {
     // the factor of the gridded values (src_slot: 0 the one the grid pass stored; 1 the l2-ball
-    // factor c = rho2 max(0, 1 - epsilon / ||Bv||) from the fused pass's per-chunk partials,
+    // factor c = rho2 max(0, 1 - epsilon / ||Bv||) from the per-chunk partials of ||Bv||^2,
     // reduced by every workgroup in the same fixed order and stored, with ||Bv||^2, by the
-    // problem's first; 2 one; 3 the first or the second, as the problem's route is)
+    // problem's first; 2 one; 3 the first or the second, by the problem's chunk_norm)
     // The sum shares the staging's barrier: its wave totals go to LDS with the tables, and the
     // factor is worked out while the gathers are in flight.
-    if (src_slot == 3) src_slot = P.fused_vis;
+    if (src_slot == 3) src_slot = P.chunk_norm;
     const int ntg = P.ntile_side_g;
     trow0 = line0 / kGridTile - 1;
     const int ntr = min(K - 1, line0 + lines - 1) / kGridTile - trow0 + 1;

@@ -22,7 +22,7 @@ __global__ void __launch_bounds__(kGridThreads, sizeof(R) == 8 ? 2 : 4)
 grid_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int src_slot, int use_cfac, int ce) {
   __shared__ unsigned long long acc[8 * (kGridTile + T - 1) * (kGridTile + T - 1)];
   extern __shared__ __align__(16) unsigned char stage_raw[];
-  __shared__ double red[2 * (kGridThreads / 64)];
+  __shared__ double red[kGridRed];
   const int4 it = items[blockIdx.x];
   grid_item<R, MODE, T>(descs[it.x], it, src_slot, use_cfac, ce, acc, stage_raw, red);
 }
@@ -33,22 +33,9 @@ degrid_grid_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ 
                    int ce) {
   __shared__ unsigned long long acc[8 * (kGridTile + T - 1) * (kGridTile + T - 1)];
   extern __shared__ __align__(16) unsigned char stage_raw[];
-  __shared__ double red[2 * (kGridThreads / 64)];
+  __shared__ double red[kGridRed];
   const int4 it = items[blockIdx.x];
   degrid_grid_item<R, MODE, T>(descs[it.x], it, src_slot, out_slot, ce, acc, stage_raw, red);
-}
-
-// P7 of a batch that mixes problems on the two routes: the fused pass for those that take it
-template <typename R, int T>
-__global__ void __launch_bounds__(kGridThreads, sizeof(R) == 8 ? 2 : 4)
-grid_mixed_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int ce) {
-  __shared__ unsigned long long acc[8 * (kGridTile + T - 1) * (kGridTile + T - 1)];
-  extern __shared__ __align__(16) unsigned char stage_raw[];
-  __shared__ double red[2 * (kGridThreads / 64)];
-  const int4 it = items[blockIdx.x];
-  const ProbDesc& P = descs[it.x];
-  if (P.fused_vis) degrid_grid_item<R, GR_DUAL, T>(P, it, VIS_BV, VIS_BV, ce, acc, stage_raw, red);
-  else grid_item<R, GR_DUAL, T>(P, it, VIS_BV, 0, ce, acc, stage_raw, red);
 }
 
 template <typename R, int T>
@@ -124,17 +111,6 @@ void launch_degrid_grid(int mode, const LaunchArgs& a, int taps, int src_slot, i
   else launch_degrid_grid_t<R, 8>(mode, a, src_slot, out_slot);
 }
 
-template <typename R>
-void launch_grid_mixed(const LaunchArgs& a, int taps) {
-  if (a.nitems <= 0) return;
-  const dim3 grid(a.nitems), block(kGridThreads);
-  const int ce = a.grid_ce;
-  const size_t shm = grid_stage_bytes<R>(ce);
-  if (taps == 4) hipLaunchKernelGGL((grid_mixed_kernel<R, 4>), grid, block, shm, a.stream, a.descs, a.items, ce);
-  else if (taps == 6) hipLaunchKernelGGL((grid_mixed_kernel<R, 6>), grid, block, shm, a.stream, a.descs, a.items, ce);
-  else hipLaunchKernelGGL((grid_mixed_kernel<R, 8>), grid, block, shm, a.stream, a.descs, a.items, ce);
-}
-
 // Raise the dynamic-LDS limit of the de-grid / grid kernels once, outside any graph capture.
 template <typename R, int T>
 void set_degrid_limits_t(int max_ts) {
@@ -145,7 +121,6 @@ void set_degrid_limits_t(int max_ts) {
   hip_check(hipFuncSetAttribute((const void*)degrid_grid_kernel<R, GR_DUAL, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   hip_check(hipFuncSetAttribute((const void*)degrid_grid_kernel<R, GR_PLAIN, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   hip_check(hipFuncSetAttribute((const void*)degrid_grid_kernel<R, GR_STOKES, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
-  hip_check(hipFuncSetAttribute((const void*)grid_mixed_kernel<R, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_st), "attr");
   const int W = max_ts + T - 1;
   const int shm_dg = W * W * (int)sizeof(Cell<R>);
   hip_check(hipFuncSetAttribute((const void*)degrid_kernel<R, DG_DUAL, T>, hipFuncAttributeMaxDynamicSharedMemorySize, shm_dg), "attr");
@@ -176,8 +151,6 @@ template void launch_degrid<float>(int, const LaunchArgs&, int, int, int, int);
 template void launch_degrid<double>(int, const LaunchArgs&, int, int, int, int);
 template void launch_grid<float>(int, const LaunchArgs&, int, int, int);
 template void launch_grid<double>(int, const LaunchArgs&, int, int, int);
-template void launch_grid_mixed<float>(const LaunchArgs&, int);
-template void launch_grid_mixed<double>(const LaunchArgs&, int);
 template void launch_degrid_grid<float>(int, const LaunchArgs&, int, int, int);
 template void launch_degrid_grid<double>(int, const LaunchArgs&, int, int, int);
 

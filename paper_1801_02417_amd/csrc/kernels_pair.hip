@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(256) p5_analysis_kernel(Pair q) {
 }
 
 constexpr size_t acc_bytes(int T) { return sizeof(unsigned long long) * 8 * (kGridTile + T - 1) * (kGridTile + T - 1); }
-constexpr size_t kRedBytes = sizeof(double) * 2 * (kGridThreads / 64);
+constexpr size_t kRedBytes = sizeof(double) * kGridRed;
 
 // the fused P6 + P7 with the coarse levels
 template <typename R, int T>

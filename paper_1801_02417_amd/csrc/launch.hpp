@@ -36,8 +36,8 @@ enum DegridMode { DG_DUAL = 0, DG_FORWARD = 1, DG_RESIDUAL = 2, DG_STOKES = 3 };
 enum GridMode { GR_DUAL = 0, GR_PLAIN = 1, GR_STOKES = 2 };
 
 // pass 2 (P8) takes src_slot as the factor mode of the gridded values: 0 the factor the grid
-// pass stored, 1 the l2-ball factor of the fused pass's partials, 2 one, 3 one of the first two by
-// the problem's fused_vis
+// pass stored, 1 the l2-ball factor of the per-chunk partials, 2 one, 3 one of the first two by
+// the problem's chunk_norm
 template <typename R> void launch_fft(int pass, const LaunchArgs& a, int cells, int src_slot, int dst_slot);
 template <typename R> void launch_primal_fft(int mode, const LaunchArgs& a, int cells);
 // P9 of one iteration with P1 and P4 of the next (row work list)
@@ -48,9 +48,6 @@ template <typename R> void launch_grid(int mode, const LaunchArgs& a, int taps, 
 // the dual B step, then grid Bv; GR_STOKES: Algorithm 3's residual, then grid it; GR_PLAIN: grid
 // phi's rows, storing none); the column inverse FFT after it takes factor mode 1 (GR_DUAL) or 2
 template <typename R> void launch_degrid_grid(int mode, const LaunchArgs& a, int taps, int src_slot, int out_slot);
-// P7 (GR_DUAL) of the problems that run P6 and P7 as two passes and the fused pass of the others
-// (ProbDesc::fused_vis), in one launch
-template <typename R> void launch_grid_mixed(const LaunchArgs& a, int taps);
 template <typename R> void set_grid_kernel_limits(int max_ts, int taps);
 void hip_check(hipError_t e, const char* what);
 template <typename R> void launch_primal(int mode, const LaunchArgs& a);

@@ -10,14 +10,19 @@
 // its visibilities over the tile plus halo in LDS and write that region to a partial slot of
 // their own with plain stores; the column inverse FFT sums the slots covering each cell in a
 // fixed order, so no global atomics are used.  Both also exist as one fused pass over the
-// gridding chunks (a chunk's taps all lie in the region it accumulates), which the iterations
-// use unless a SARA branch runs on a stream beside them.
+// gridding chunks (a chunk's taps all lie in the region it accumulates).
 //
 // The dual variable B is kept as B = c * Bv: the de-gridding pass writes
-// Bv = B/rho2 + phi(X) - Y and the FP64 partial sums of ||Bv||^2; the gridding pass reduces
-// those partials (fixed order, compensated) to c = rho2 * max(0, 1 - epsilon/||Bv||), which
-// both it and the next iteration's de-gridding apply on the fly.  This equals
+// Bv = B/rho2 + phi(X) - Y, and c = rho2 * max(0, 1 - epsilon/||Bv||), from FP64 partial sums of
+// ||Bv||^2 (fixed order, compensated), is applied on the fly by the column inverse FFT to the
+// gridded values and by the next iteration's de-gridding to Bv.  This equals
 // B~ - rho2 P_B(Y,eps)(B~/rho2) without a second pass over the visibilities.
+//
+// A problem whose iterations may take either route (ProbDesc::chunk_norm) has its partial sums by
+// gridding chunk, from the fused pass or from the gridding pass, and both routes compute every
+// number alike, so a launch takes the route that suits its whole set of problems and a
+// member of a batch still gets the bits of its run alone.  The others, which run the two passes
+// in every launch but the initialisation's, have them by de-grid item.
 #pragma once
 
 #include <type_traits>
@@ -29,7 +34,8 @@ namespace psara {
 
 // ---------------------------------------------------------------------------------------------
 // Pieces shared by the de-grid, grid and fused passes (one definition, so that the fused pass
-// computes exactly what the separate ones do).
+// computes exactly what the separate ones do, bit for bit: where the fused pass cuts the work
+// differently, it keeps the order of the sums).
 
 // v_s = sum_j w2[j] sum_i w1[i] win[(r2 + j) * ws + r1 + i].s: the T x T taps of a window held
 // in LDS as k2-major rows of ws cells
@@ -91,6 +97,17 @@ __device__ inline RowIn<R> row_inputs(const ProbDesc& P, long long m, int src_sl
   return r;
 }
 
+// Adds the squared moduli of a row's eight reals to acc.  (The products are rounded on their own,
+// so that the pass that makes the row and the one that reads it add the same numbers.)
+template <typename R>
+__device__ __forceinline__ void add_row_norm(const Cell<R>& o, KSum& acc) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    acc.add(mul_rn((double)o.s[s].re, (double)o.s[s].re));
+    acc.add(mul_rn((double)o.s[s].im, (double)o.s[s].im));
+  }
+}
+
 // The de-grid pass's row m for MODE (not DG_FORWARD) from its de-gridded Stokes values and its
 // inputs, with the squared moduli of its eight reals added to acc.  DG_DUAL: Bv = cb Bv_old +
 // phi - Y (cb = c/rho2); DG_RESIDUAL: Y - phi; DG_STOKES: per Stokes map Phi S - Y L^{-1}
@@ -120,12 +137,7 @@ __device__ inline Cell<R> degrid_row_in(const ProbDesc& P, int m, const cplx<R> 
       for (int s = 0; s < 4; ++s) o.s[s] = csub(y.s[s], phi.s[s]);
     }
   }
-#pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const double re = (double)o.s[s].re, im = (double)o.s[s].im;
-    acc.add(re * re);
-    acc.add(im * im);
-  }
+  add_row_norm<R>(o, acc);
   return o;
 }
 
@@ -253,7 +265,8 @@ __device__ __forceinline__ void degrid_item(const ProbDesc& P, const int4 it, in
       else out[m] = degrid_row<R, MODE>(P, m, v, src_slot, acc);
     }
   }
-  if (MODE != DG_FORWARD) {
+  // (the dual step's norm of a problem with chunk_norm is summed by gridding chunk)
+  if (MODE != DG_FORWARD && !(MODE == DG_DUAL && P.chunk_norm)) {
     const KSum tot = block_reduce(acc, red);
     if (threadIdx.x == 0) {
       P.partials[2 * part] = tot.s;
@@ -293,8 +306,9 @@ __device__ __forceinline__ void degrid_item(const ProbDesc& P, const int4 it, in
 // B, which the gridding leaves out: one item per problem (kGridFactorItem, first in the work
 // list, so it runs beside the chunks)
 // stores that factor -- GR_DUAL: c, reduced in a fixed order from the de-grid partials and
-// also kept for the next iteration; GR_PLAIN: 1, or the stored c when use_cfac is set;
-// GR_STOKES: 1.
+// also kept for the next iteration (with chunk_norm nothing: the chunks leave their partials of
+// ||Bv||^2, from which the column inverse FFT works c out); GR_PLAIN: 1, or the stored c when
+// use_cfac is set; GR_STOKES: 1.
 //
 // Fixed-point terms of the LDS accumulation: conv(a, fx) is the term of a * fx (fx a power of
 // two, so a * fx is exact), value(sum) the nearest-integer sum of the terms it received.
@@ -492,25 +506,63 @@ __device__ inline void grid_chunk(const ProbDesc& P, const int4 ch,
   }
 }
 
-// The taps of one row shared by the lanes of a group of eight: this lane's tap row (its eight
-// cells at row, its weight w2, 0 for lanes beyond T), and the sum over the group to every lane.
+// One row interpolated by a group of eight lanes: the lane sums its tap row (its eight cells at
+// row), and the rows are added with their weights (w2: the lane's) in the order of interpolate(),
+// so the result has its bits.  Valid in the group's lanes 0 .. 3.
 template <typename R, int T>
 __device__ inline void interpolate_row(const Cell<R>* row, const R* w1, R w2, cplx<R> v[4]) {
+  cplx<R> t[4], m[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) v[s] = cmk(R(0), R(0));
+  for (int s = 0; s < 4; ++s) t[s] = cmk(R(0), R(0));
 #pragma unroll
   for (int i = 0; i < T; ++i) {
     const Cell<R> c = row[i];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) { v[s].re += w1[i] * c.s[s].re; v[s].im += w1[i] * c.s[s].im; }
+    for (int s = 0; s < 4; ++s) { t[s].re += w1[i] * c.s[s].re; t[s].im += w1[i] * c.s[s].im; }
   }
-  auto group_sum = [](R x) {
-    x += dpp_move<0xB1>(x);                        // lane ^ 1
-    x += dpp_move<0x4E>(x);                        // lane ^ 2
-    return x + half_mirror(x);                     // the other quad
-  };
+  const R wm = half_mirror(w2);
 #pragma unroll
-  for (int s = 0; s < 4; ++s) v[s] = cmk(group_sum(v[s].re * w2), group_sum(v[s].im * w2));
+  for (int s = 0; s < 4; ++s) {
+    m[s] = cmk(half_mirror(t[s].re), half_mirror(t[s].im));
+    v[s] = cmk(R(0), R(0));
+  }
+  static_for<0, T>([&](auto jc) {
+    constexpr int j = decltype(jc)::value, k = j < 4 ? j : 7 - j;
+    const R wj = quad_bcast<k>(j < 4 ? w2 : wm);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      v[s].re += wj * quad_bcast<k>(j < 4 ? t[s].re : m[s].re);
+      v[s].im += wj * quad_bcast<k>(j < 4 ? t[s].im : m[s].im);
+    }
+  });
+}
+
+// A chunk of at most this many rows has, in FP32, eight lanes to a row in the fused pass (see
+// there); the gridding pass deals its rows to the same threads, for the same sums.  (The test is
+// written out where it is used: folded in the front end, it keeps the FP64 kernels free of spills.)
+constexpr int kFewRows = kGridThreads / 8;
+
+// The sums over a chunk's rows, from each thread's: the bound of the fixed point (returned to every
+// thread) and, with nrm, ||Bv||^2 to the chunk's pair of chunk_partials.  One barrier, after which
+// the entries that the threads have staged are visible.  (A thread's bound is a KSum for the branches
+// in its add: with a plain sum the compiler runs the fused FP64 pass's two rows into one another and spills.)
+constexpr int kGridRed = 3 * (kGridThreads / 64);      // doubles of shared memory
+__device__ __forceinline__ double chunk_sums(const ProbDesc& P, int slot, bool nrm, KSum norm, double bound, double* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (nrm) norm = wave_reduce(norm);
+  for (int off = 32; off > 0; off >>= 1) bound += __shfl_xor(bound, off, 64);
+  if (lane == 0) { red[3 * wave] = norm.s; red[3 * wave + 1] = norm.c; red[3 * wave + 2] = bound; }
+  __syncthreads();
+  double total = 0.0;
+  for (int w = 0; w < kGridThreads / 64; ++w) total += red[3 * w + 2];
+  if (nrm && threadIdx.x == 0) {
+    KSum t;
+    for (int w = 0; w < kGridThreads / 64; ++w) { KSum o; o.s = red[3 * w]; o.c = red[3 * w + 1]; t.merge(o); }
+    double* pp = chunk_partials(P);
+    pp[2 * slot] = t.s;
+    pp[2 * slot + 1] = t.c;
+  }
+  return total;
 }
 
 // A value of lane e (e the same in every lane), read into a scalar register.
@@ -530,7 +582,8 @@ __device__ inline V lane_value(V v, int e) {
 // q = lane + 64 k of the chunk's box and adds, entry by entry in list order, the entry's tap
 // product times its channels -- a fixed order, so the sums are deterministic like the
 // fixed-point sums of the larger chunks.  Lanes 0..T-1 evaluate the entry's k1 taps and lanes
-// 8..8+T-1 its k2 taps; a cell takes the two it needs by a lane shuffle.
+// 8..8+T-1 its k2 taps; a cell takes the two it needs by a lane shuffle.  The fused pass has the
+// same sums (grid_small_wg).
 template <typename R, int MODE, int T>
 __device__ inline void grid_small(const ProbDesc& P, const int4 it, int src_slot) {
   static_assert(T <= 8 && kSmallChunk <= 64, "eight taps and an entry per lane");
@@ -556,7 +609,31 @@ __device__ inline void grid_small(const ProbDesc& P, const int4 it, int src_slot
   const V2<R> fm = ((const V2<R>*)P.vis_frac)[m];
   const int pkm = P.vis_k0[m];
   V4<R> u0, u1;
-  (void)grid_channels<R, MODE>(P, m, ((const Cell<R>*)P.vis[src_slot])[m], u0, u1);
+  const Cell<R> b = ((const Cell<R>*)P.vis[src_slot])[m];
+  (void)grid_channels<R, MODE>(P, m, b, u0, u1);
+  if (MODE == GR_DUAL && P.chunk_norm) {
+    // as a workgroup sums it (chunk_sums): FP64 has the chunk's rows on the lanes of its
+    // first wave, FP32 eight rows to a wave (kFewRows), one to every eighth lane
+    KSum k, t;
+    if (lane < ne) add_row_norm<R>(b, k);
+    for (int off = sizeof(R) == 4 ? 4 : 32; off > 0; off >>= 1) {
+      KSum o;
+      o.s = __shfl_xor(k.s, off, 64);
+      o.c = __shfl_xor(k.c, off, 64);
+      k.merge(o);
+    }
+    for (int w = 0; w < (sizeof(R) == 4 ? kSmallChunk / 8 : 1); ++w) {
+      KSum o;
+      o.s = __shfl(k.s, 8 * w, 64);
+      o.c = __shfl(k.c, 8 * w, 64);
+      t.merge(o);
+    }
+    if (lane == 0) {
+      double* pp = chunk_partials(P);
+      pp[2 * ch.w] = t.s;
+      pp[2 * ch.w + 1] = t.c;
+    }
+  }
 
   const int ntg = P.ntile_side_g;
   const int t1 = ch.x / ntg, t2 = ch.x - t1 * ntg;
@@ -601,6 +678,50 @@ __device__ inline void grid_small(const ProbDesc& P, const int4 it, int src_slot
   }
 }
 
+// The same chunk by a whole workgroup of the fused pass, which has staged the entries' offsets (sf)
+// and channels (su) and, at st, their window starts relative to the tile (o1 | o2 << 8): a thread
+// owns a cell of the box or two, and finds the taps in LDS (sw: 16 per entry, k1 then k2).  Each
+// cell gets the sum that grid_small gives it.  No zeroing of the fixed-point tile, no atomics.
+template <typename R, int T>
+__device__ inline void grid_small_wg(const ProbDesc& P, const int4 ch, int ne, const V2<R>* sf, const V4<R>* su,
+                                     const int* st, R* sw, int box) {
+  constexpr int RG = kGridTile + T - 1;
+  static_assert(16 * kSmallChunk <= kGridThreads, "a thread per tap");
+  R cr[KbDeg<R>::value + 1];
+  load_poly<R, T>(P, cr);
+  __syncthreads();                                 // the entries are staged
+  if (threadIdx.x < 16 * ne) {
+    const V2<R> f = sf[threadIdx.x >> 4];
+    sw[threadIdx.x] = kb_tap<R, T>(R(2) * ((threadIdx.x & 8) ? f.y : f.x) - R(T - 1), cr);
+  }
+  __syncthreads();
+  const int lo1 = box & 255, lo2 = (box >> 16) & 255;
+  const int bw = ((box >> 8) & 255) - lo1 + 1, area = bw * (((box >> 24) & 255) - lo2 + 1);
+  const float rbw = 1.0f / (float)bw;
+  Cell<R>* __restrict__ dst = (Cell<R>*)P.gpart + (size_t)ch.w * RG * RG;
+#pragma unroll 1
+  for (int q = threadIdx.x; q < area; q += kGridThreads) {
+    const int a = small_div(q, rbw), c1 = lo1 + q - a * bw, c2 = lo2 + a;
+    R acc[8];
+#pragma unroll
+    for (int h = 0; h < 8; ++h) acc[h] = R(0);
+#pragma unroll 2
+    for (int e = 0; e < ne; ++e) {
+      const V4<R> v0 = su[2 * e], v1 = su[2 * e + 1];
+      const R u[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+      const int s = st[e], i = c1 - (s & 255), j = c2 - (s >> 8);
+      const R wi = sw[16 * e + (i & 7)], wj = sw[16 * e + 8 + (j & 7)];
+      const R ww = ((unsigned)i < (unsigned)T && (unsigned)j < (unsigned)T) ? wi * wj : R(0);
+#pragma unroll
+      for (int h = 0; h < 8; ++h) acc[h] += ww * u[h];
+    }
+    Cell<R> o;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) o.s[h] = cmk(acc[2 * h], acc[2 * h + 1]);
+    dst[c2 * RG + c1] = o;
+  }
+}
+
 // (ce: the largest chunk of the launch's problems; the staging arrays after the accumulator hold
 // ce entries)
 template <typename R, int MODE, int T>
@@ -617,6 +738,7 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
   if (it.y == kGridFactorItem) {   // the factor item: the factor the column inverse FFT applies
     if (halted(P)) return;
     if (MODE == GR_DUAL) {
+      if (P.chunk_norm) return;
       const double v2 = block_sum_partials(P.partials, P.n_p6, red);
       if (threadIdx.x == 0) {
         const double vn = sqrt(v2);
@@ -635,10 +757,12 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
   static_assert(kChunkEntries <= 2 * kGridThreads, "two entries per thread");
   const int2 ent = make_int2(it.z, it.w);
   const int ne = ent.y - ent.x;
+  const bool few = sizeof(R) == 4 && ne <= kFewRows;
+  const int q0 = few ? threadIdx.x >> 3 : threadIdx.x, qs = few ? kGridThreads / 8 : kGridThreads;
   int me[2];
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const int q = threadIdx.x + e * blockDim.x;
+    const int q = q0 + e * qs;
     me[e] = ent.x + (q < ne ? q : 0);                      // the chunk's rows are contiguous
   }
   const int4 ch = P.chunks[it.y];
@@ -659,19 +783,21 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
     be[e] = bsrc[me[e]];
   }
   for (int q = threadIdx.x; q < 8 * RG * RG; q += blockDim.x) acc[q] = 0ull;
-  KSum bound;
+  KSum bound, norm;
+  const bool nrm = MODE == GR_DUAL && P.chunk_norm;
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    const int q = threadIdx.x + e * blockDim.x;
-    if (q >= ne) break;
+    const int q = q0 + e * qs;
+    if (q >= ne || (few && (threadIdx.x & 7) != 0)) break;
     sf[q] = fe[e];
     V4<R> u0, u1;
     const R mx = grid_channels<R, MODE>(P, me[e], be[e], u0, u1);
     su[2 * q] = u0;
     su[2 * q + 1] = u1;
     bound.add((double)mx);
+    if (nrm) add_row_norm<R>(be[e], norm);
   }
-  const double total = block_reduce(bound, red).value();      // includes a barrier
+  const double total = chunk_sums(P, ch.w, nrm, norm, bound.value(), red);
   grid_chunk<R, T, kPoly>(P, ch, sf, su, acc, fixed_exponent<R>(total), pre);
 }
 
@@ -692,7 +818,6 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
 // 64^2 34.4 -> 33.0, initialisation of 256^2 / 2e5 65.5 -> 64.0 and of 512^2 / 1e6 206 -> 200, TV at
 // 256^2 65.2 -> 63.7; with two passes (128 rows) 128^2 with Mueller matrices lost 1.5 %.  Not in
 // FP64, where the lanes' polynomials cost registers that spill (32^2 39.0 -> 41.1).
-constexpr int kFewRows = kGridThreads / 8;
 template <typename R, int MODE, int T>
 __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 it, int src_slot, int out_slot, int ce,
                                                  unsigned long long* acc, unsigned char* stage_raw, double* red) {
@@ -738,6 +863,12 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
   });
   __syncthreads();
 
+  // (a small chunk's tables, behind its entries: the windows' starts, then the taps)
+  const bool small = ne <= kSmallChunk;
+  int* st = (int*)(su + 2 * kSmallChunk);
+  R* sw = (R*)(su + 2 * kSmallChunk + kSmallChunk / 4);
+  static_assert(kSmallChunk % 4 == 0 && 16 * kSmallChunk / 4 + 2 * kSmallChunk + kSmallChunk / 4 <= 2 * kLeastChunk,
+                "the tables fit the staging of the smallest chunk size");
   Cell<R>* __restrict__ out = (Cell<R>*)P.vis[out_slot];
   KSum bound, norm;
 #pragma unroll
@@ -775,15 +906,13 @@ __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 i
     su[2 * q + 1] = u1;
     bound.add((double)mx);
   }
-  if constexpr (kStore) {
-    const KSum nt = block_reduce(norm, red);
-    if (threadIdx.x == 0) {
-      double* pp = chunk_partials(P);
-      pp[2 * ch.w] = nt.s;
-      pp[2 * ch.w + 1] = nt.c;
-    }
+  if (small) {
+    if (q0 < ne) st[q0] = ((pke[0] >> 16) - b1) | (((pke[0] & 0xffff) - b2) << 8);
+    if (kStore) chunk_sums(P, ch.w, true, norm, bound.value(), red);
+    grid_small_wg<R, T>(P, ch, ne, sf, su, st, sw, pre.box);
+    return;
   }
-  const double total = block_reduce(bound, red).value();       // barriers: the window is done
+  const double total = chunk_sums(P, ch.w, kStore, norm, bound.value(), red);       // a barrier: the window is done
   for (int q = threadIdx.x; q < 8 * RG * RG; q += blockDim.x) acc[q] = 0ull;
   __syncthreads();
   grid_chunk<R, T, false>(P, ch, sf, su, acc, fixed_exponent<R>(total), pre);
