@@ -499,7 +499,8 @@ __device__ __forceinline__ void synthesis_final_item(const ProbDesc& P, const in
 // analysis turns it level by level into the Mallat pyramid of the coarse levels, in place; every
 // coefficient's dual update follows, and synthesis runs back in place from level L to level c on
 // the updated duals and leaves the low-low band of level c-1 in the level scratch, where the
-// next synthesis launch reads it.  Replaces 2 (L - c + 1) small launches by one.
+// next synthesis launch reads it.  Replaces 2 (L - c + 1) small launches by one, with the same
+// bits, so that the first coarse level may follow the launch shapes.
 // items: {prob, wavelet index (-1: none), Stokes channel, first coarse level c}
 //
 // In place without a second buffer: a filter pass runs along lines (rows or columns) of m <= 128
@@ -531,8 +532,10 @@ __device__ __forceinline__ void coarse_step(R* b, const int* lo, int hi, int oa,
     for (int j = 0; j < F / 2; ++j) { x[j] = b[lo[j]]; y[j] = b[lo[j] + hi]; }
 #pragma unroll
     for (int j = 0; j < F / 2; ++j) {
-      a0 += t.h[2 * j] * x[j] + t.g[2 * j] * y[j];
-      a1 += t.h[2 * j + 1] * x[j] + t.g[2 * j + 1] * y[j];
+      a0 += t.h[2 * j] * x[j];                     // (the order of syn_filter)
+      a0 += t.g[2 * j] * y[j];
+      a1 += t.h[2 * j + 1] * x[j];
+      a1 += t.g[2 * j + 1] * y[j];
     }
   } else {
     R x[F];

@@ -217,7 +217,17 @@ void check_tuning(const Tuning& t, int K) {
 // in every launch: beside a SARA branch on another stream the fused pass's workgroups share the
 // CUs worse (us per iteration, fused -> two passes: 512^2 / 1e6 rows 282 -> 269, with one wavelet level
 // 258 -> 246, 1024^2 / 1e6 with one level 743 -> 640, 512^2 / 3e5 FP64 with one level 427 -> 382).
+// (c_level: the first coarse level of the default shapes, so that the shapes do not change the sums.)
 static bool chunk_norm(int K, int levels, int c_level) { return K <= 512 && (levels < 2 || c_level <= 2); }
+
+// Whether the first analysis level of problems of sides up to n is paired under this tiling.  Not the
+// items that run every basis over a tile where there are few large ones (16-wide tiles, FP64): they
+// hold up P5, and are better off on another stream (us per iteration, paired / apart: 256^2 / 2e5 rows
+// 113 / 103, 128^2 FP64 75 / 70; with 8-wide tiles 93 / 97 at 256^2, 51 / 59 at 128^2).
+template <typename R>
+static bool pair_tiles(int n, int ana_wide) {
+  return !(ana_wide & kAnaAllBases) || (sizeof(R) == 4 && dwt_ana_tile<R>(n >> 1, (ana_wide & kAnaWide) != 0) <= 8);
+}
 
 // ------------------------------------------------------------------------------------------------
 // work lists (appended per problem, so batches concatenate them)
@@ -586,6 +596,12 @@ void Engine<R>::build_prior_items() {
 }
 
 template <typename R>
+void Engine<R>::choose_levels() {
+  c_level_ = coarse_level<R>(geo_.n, h_.levels, cells_ == 512 && pair_tiles<R>(geo_.n, tuning_.ana_wide));
+  h_.chunk_norm = chunk_norm(geo_.K, h_.levels, coarse_level<R>(geo_.n, h_.levels, true)) ? 1 : 0;
+}
+
+template <typename R>
 void Engine<R>::set_tuning(const Tuning& t) {
   check_tuning(t, geo_.K);
   hip_check(hipStreamSynchronize(s0_), "tuning sync");
@@ -599,6 +615,7 @@ void Engine<R>::set_tuning(const Tuning& t) {
   rcells_ = cells_;
   h_.dg_item = t.degrid_item;
   h_.ana_wide = t.ana_wide;
+  if (has_prior()) choose_levels();
   build_operator_items();
   build_prior_items();
   realloc_partials();
@@ -637,6 +654,7 @@ void Engine<R>::upload_items() {
   pl_.sparse = h_.coef[COEF_A] != nullptr && h_.nwav > 0;
   pl_.tv = h_.tv_kind != 0;
   pl_.chunk_norm = h_.chunk_norm != 0;
+  pl_.one_level = one_level();
   pl_.vis = geo_.M;
 }
 
@@ -776,8 +794,7 @@ void Engine<R>::set_prior(uint32_t mask, int levels, const double* weights, doub
   for (size_t i = 0; i < gw.size(); ++i) gw[i] = (R)(gamma * (weights ? weights[i] : 1.0));
   copy_sync(h_.coef[COEF_GW], gw.data(), gw.size() * sizeof(R), hipMemcpyHostToDevice, s0_, "weights upload");
   zero(h_.coef[COEF_A], coef_elems_ * sizeof(V4<R>));
-  c_level_ = coarse_level<R>(n, levels);
-  h_.chunk_norm = chunk_norm(geo_.K, levels, c_level_) ? 1 : 0;
+  choose_levels();
   build_prior_items();
   realloc_partials();
   upload_items();
@@ -841,13 +858,14 @@ void launch_sara_dual(const PassLists& L, hipStream_t s) {
 
 // Whether the prior's branch runs inside the data branch's launches (kernels_pair.hip) rather
 // than on a stream of its own: where it has no more stages than the data branch has passes
-// between the row passes (every problem's SARA branch by chunk_norm(), and the TV priors).
+// between the row passes (a SARA branch with one analysis level before the coarse ones, and the
+// TV priors).
 //   us per iteration, apart -> paired: 32^2 FP64 50.4 -> 46.6, 64^2 41.9 -> 37.6, 128^2 51.5 ->
 //   47.9, 256^2 94.3 -> 84.8, TV at 256^2 76.0 -> 65.7.  With two analysis levels, as P5 | level 1,
 //   P6 | level 2, P7 | coarse, P8 | level 2, the final synthesis alone: 256^2 97.9, 128^2 FP64
 //   83.4 (71.1 apart), since every pair waits for the longer of its two and the fused P6 + P7 has
 //   no place.
-// The pair kernels exist for 512 FFT cells per workgroup, and not for the all-bases tiling.  A
+// The pair kernels exist for 512 FFT cells per workgroup.  A
 // launch of more than kMaxPaired gridding chunks (a large batch, or very many rows) fills the GPU from
 // either branch, and the two share it better on their own streams; FP64 has one gridding
 // workgroup to a CU, FP32 up to four.
@@ -864,7 +882,7 @@ template <typename R>
 bool paired(const PassLists& L, int mode) {
   if (L.cells != 512) return false;
   if (pm_tv(mode)) return true;
-  return mode != PM_INIT && L.sparse && L.chunk_norm && !(L.ana_wide & kAnaAllBases) &&
+  return mode != PM_INIT && L.sparse && L.chunk_norm && L.one_level && pair_tiles<R>(L.max_n, L.ana_wide) &&
          L.p7f.count <= kMaxPaired<R>;
 }
 
@@ -1647,9 +1665,10 @@ Batch<R>::Batch(const std::vector<Engine<R>*>& members, hipStream_t stream) : me
   pl_.ana_wide = ana_wide;
   pl_.grid_ce = grid_ce;
   pl_.sparse = sparse;
-  pl_.chunk_norm = true;
+  pl_.chunk_norm = pl_.one_level = true;
   for (Engine<R>* e : members_) {
     pl_.chunk_norm = pl_.chunk_norm && e->desc().chunk_norm != 0;
+    pl_.one_level = pl_.one_level && e->one_level();
     pl_.vis += e->geometry().M;
   }
   set_grid_kernel_limits<R>(max_ts, T);

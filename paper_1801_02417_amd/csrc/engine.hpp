@@ -92,6 +92,7 @@ struct PassLists {
   int ana_wide = 1;                // the problems' analysis tilings (kAnaWide | kAnaAllBases bits)
   int grid_ce = kChunkEntries;     // largest gridding chunk among the problems
   bool chunk_norm = false;         // every problem has ProbDesc::chunk_norm
+  bool one_level = false;          // ... and at most one analysis level before the coarse ones
   long long vis = 0;               // visibilities of all problems
   bool sparse = false;             // every problem has a wavelet prior (P2/P3 run)
   bool tv = false;                 // the problems carry a TV prior (Algorithm 3)
@@ -171,6 +172,7 @@ struct Engine {
   hipStream_t stream() const { return s0_; }
   const Geometry& geometry() const { return geo_; }
   int c_level() const { return c_level_; }
+  bool one_level() const { return h_.levels < 2 || c_level_ <= 2; }
   bool has_prior() const { return h_.coef[COEF_A] != nullptr && h_.nwav > 0; }
   void sync() { sync_desc(); }
 
@@ -201,6 +203,7 @@ struct Engine {
   void upload_chunks();                              // the geometry's runs, chunks and slots
   void build_operator_items();
   void build_prior_items();
+  void choose_levels();      // the first coarse level, and whether ||Bv||^2 is summed by chunk
   void prime(int mode);       // Algorithm 3: the data gradient and Psi A of the current state
   void adaptive_buffers();
   void forward(int src_img, int mode, int out_vis);

@@ -56,10 +56,14 @@ coarse_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items
 }
 
 template <typename R>
-int coarse_level(int n, int levels) {
+int coarse_level(int n, int levels, bool pairable) {
   // first level >= 2 whose input low-low band fits; the largest only where it spares the branch
-  // its second analysis launch (sides up to twice that)
-  const int most = n <= 2 * CoarseMax<R>::value ? CoarseMax<R>::value : CoarseMax<R>::value / 2;
+  // its second analysis launch (sides up to twice that), and in FP32 only where the branch may run in
+  // the data passes' launches: beside them on another stream the workgroups of 128^2 are the longer
+  // ones (256^2 with 1024 FFT cells to a workgroup: 103 us per iteration, 94 with 64^2; FP64's largest,
+  // 64^2, takes a quarter of the time, and with half of it 128^2 needs the extra launches)
+  const bool whole = n <= 2 * CoarseMax<R>::value && (pairable || sizeof(R) == 8);
+  const int most = whole ? CoarseMax<R>::value : CoarseMax<R>::value / 2;
   for (int c = 2; c <= levels; ++c)
     if ((n >> (c - 1)) <= most) return c;
   return levels + 1;
@@ -144,8 +148,8 @@ template void launch_synthesis<double>(int, int, const LaunchArgs&, int, int);
 template void launch_synthesis_final<float>(const LaunchArgs&, int, int, int, int);
 template void launch_coarse<float>(const LaunchArgs&);
 template void launch_coarse<double>(const LaunchArgs&);
-template int coarse_level<float>(int, int);
-template int coarse_level<double>(int, int);
+template int coarse_level<float>(int, int, bool);
+template int coarse_level<double>(int, int, bool);
 template void launch_synthesis_final<double>(const LaunchArgs&, int, int, int, int);
 
 }  // namespace psara

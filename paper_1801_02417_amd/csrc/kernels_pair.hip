@@ -43,17 +43,17 @@ constexpr size_t max_size() { return sizeof(A) > sizeof(B) ? sizeof(A) : sizeof(
 constexpr int kCells = 512;
 static_assert(kCoarseThreads == kGridThreads, "one workgroup size");
 
-// P5 with the first analysis level
-template <typename R, int TOM>
+// P5 with the first analysis level (SEP: with items that run every basis of a tile)
+template <typename R, int TOM, bool SEP>
 __global__ void __launch_bounds__(256) p5_analysis_kernel(Pair q) {
   using SA = FftSmem<R, kCells, 1>;
-  using SB = AnaSmem<R, TOM, false>;
+  using SB = AnaSmem<R, TOM, SEP>;
   __shared__ __align__(16) unsigned char raw[max_size<SA, SB>()];
   bool is_a;
   int4 it;
   if (!pair_item(q, is_a, it)) return;
   if (is_a) fft_pass<R, kCells, 1, -1>(q.descs[it.x], it, 0, 0, *(SA*)raw);
-  else analysis_item<R, AM_DUAL, TOM, false>(q.descs[it.x], it, 1, IMG_X, COEF_A, *(SB*)raw);
+  else analysis_item<R, AM_DUAL, TOM, SEP>(q.descs[it.x], it, 1, IMG_X, COEF_A, *(SB*)raw);
 }
 
 constexpr size_t acc_bytes(int T) { return sizeof(unsigned long long) * 8 * (kGridTile + T - 1) * (kGridTile + T - 1); }
@@ -138,10 +138,16 @@ void launch_p5_analysis(const LaunchArgs& a, const LaunchArgs& b) {
   // the largest tile side among the launch's problems, as for the analysis kernel alone
   constexpr int kWide = dwt_ana_tile<R>(1 << 30);
   const int tom = b.max_n > 0 ? dwt_ana_tile<R>(b.max_n >> 1, (b.ana_wide & kAnaWide) != 0) : kWide;
-  if (tom > 8)
-    hipLaunchKernelGGL((p5_analysis_kernel<R, kWide>), grid, dim3(256), 0, a.stream, q);
-  else
-    hipLaunchKernelGGL((p5_analysis_kernel<R, 8>), grid, dim3(256), 0, a.stream, q);
+  const bool sep = (b.ana_wide & kAnaAllBases) != 0;
+#define PSARA_P5A(TOM, SEP) hipLaunchKernelGGL((p5_analysis_kernel<R, TOM, SEP>), grid, dim3(256), 0, a.stream, q)
+  if (tom > 8) {
+    if (sep) PSARA_P5A(kWide, true);
+    else PSARA_P5A(kWide, false);
+  } else {
+    if (sep) PSARA_P5A(8, true);
+    else PSARA_P5A(8, false);
+  }
+#undef PSARA_P5A
 }
 
 template <typename R>

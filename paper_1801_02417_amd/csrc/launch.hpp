@@ -58,7 +58,7 @@ template <typename R> void launch_synthesis(int level, int coarsest, const Launc
 template <typename R> void launch_synthesis_final(const LaunchArgs& a, int src_coef, int dst_slot, int add_dirac,
                                                   int dst_slot2);
 template <typename R> void launch_coarse(const LaunchArgs& a);
-template <typename R> int coarse_level(int n, int levels);
+template <typename R> int coarse_level(int n, int levels, bool pairable);
 
 // reductions and small utility kernels (items: {prob, block, -, -})
 template <typename R> void launch_relvar(const LaunchArgs& a);

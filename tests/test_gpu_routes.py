@@ -1,7 +1,7 @@
 """P6 and P7 as two passes and as one fused pass give the same bits, so that a launch may take either:
 the paired launches of a solve with the default shapes (fused) against the launches on two streams
-that more FFT cells per workgroup ask for (two passes, or fused where the chunks are full), and
-members of a batch too large for the paired launches against their runs alone.  Chunks of every kind
+that more FFT cells per workgroup ask for (two passes, or fused where the chunks are full; at 256^2 in
+FP32 the coarse levels begin one level later there), and members of a batch too large for the paired launches against their runs alone.  Chunks of every kind
 (of one row, up to and beyond the sizes that one wave grids and that eight lanes to a row de-grid, of
 runs), every tap count, known Mueller matrices, both precisions."""
 import numpy as np
@@ -58,6 +58,8 @@ def _run(s, mode):
     (128, 4, 2, SIZES + [700], False, "CONSTRAINED"),
     (16, 8, 1, [900, 1100, 1024, 500], False, "CONSTRAINED"),      # full chunks
     (32, 8, 2, [40] * 16, True, "CONSTRAINED"),
+    (256, 8, 4, SIZES, False, "CONSTRAINED"),                      # another first coarse level, too
+    (256, 8, 3, [1000] * 40, False, "CONSTRAINED"),
 ])
 def test_routes_give_the_same_bits(n, taps, levels, sizes, mueller, mode, prec):
     uv = _uv(n, np.random.default_rng(n + taps), sizes)
