@@ -1339,44 +1339,70 @@ void Engine<R>::reweight(double delta) {
   hip_check(hipStreamSynchronize(s0_), "reweight sync");
 }
 
+// The power iteration's start: standard normal numbers by Marsaglia's polar method from a seeded
+// mt19937_64, the numbers of libstdc++'s normal_distribution.  (That one works out the generator's
+// range by two long double logarithms a draw wherever the compiler does not take them out of its loop:
+// 30 ms more at 512^2.)
+template <typename R>
+static std::vector<R> normal_start(size_t count) {
+  std::mt19937_64 rng(12345);
+  auto uniform = [&] { return std::min((double)rng() * 0x1p-64, 1.0 - 0x1p-53); };   // in [0, 1)
+  std::vector<R> x(count + count % 2);
+  for (size_t i = 0; i < x.size(); i += 2) {
+    double a, b, r2;
+    do {
+      a = 2.0 * uniform() - 1.0;
+      b = 2.0 * uniform() - 1.0;
+      r2 = a * a + b * b;
+    } while (r2 > 1.0 || r2 == 0.0);
+    const double f = std::sqrt(-2.0 * std::log(r2) / r2);
+    x[i] = (R)(b * f);
+    x[i + 1] = (R)(a * f);
+  }
+  x.resize(count);
+  return x;
+}
+
 // FP64 power iteration of S -> Re phi^dagger phi S (Rayleigh quotient of a unit vector)
 template <typename R>
 double Engine<R>::opnorm(int max_iter, double rtol, int* iters_out) {
   sync_desc();
   const size_t N = (size_t)geo_.n * geo_.n;
-  std::mt19937_64 rng(12345);
-  std::normal_distribution<double> nd(0.0, 1.0);
-  std::vector<R> x0(N * 4);
-  for (auto& v : x0) v = (R)nd(rng);
+  const std::vector<R> x0 = normal_start<R>(N * 4);
   copy_sync(h_.img[IMG_TMP2], x0.data(), x0.size() * sizeof(R), hipMemcpyHostToDevice, s0_, "x0 upload");
   launch_img_dot<R>(la(d_img_), IMG_TMP2, IMG_TMP2);
-  launch_img_normalise<R>(la(d_img_), IMG_TMP2, IMG_TMP2, SC_DOT);
+  launch_img_normalise<R>(la(d_img_), IMG_TMP2, IMG_TMP2, SC_DOT, -1, 0.0);
   // phi^dagger phi with the de-gridding and the gridding as the fused pass.  The steps are queued in
-  // rounds of kNormRound, so that the host waits once a round; it takes the quotients in order and
-  // stops at the first that meets the test, as if it had looked after each.  us a step, with two
+  // rounds of up to kNormRound, so that the host waits once a round; it takes the quotients in order and
+  // stops at the first that meets the test, as if it had looked after each.  The device makes the
+  // same test (the same operations) and halts, so the steps queued beyond that one cost their empty
+  // launches alone, and the first rounds are short, so a loose test queues few.  us a step, with two
   // passes, three launches for the sums and the scaling and a wait a step -> now: 128^2 / 2e4 rows
   // 120 -> 66, 256^2 / 2e5 360 -> 287, 512^2 / 1e6 1113 -> 942 (bound there by the FP64 gridding).
   double lam = 0.0;
   int it = 0;
   for (bool done = false; it < max_iter && !done;) {
-    const int round = std::min(kNormRound, max_iter - it);
+    const int round = std::min(std::min(kNormRound, std::max(2, it)), max_iter - it), first = it;
     for (int k = 0; k < round; ++k) {
       p4(IMG_TMP2); p5();
       launch_degrid_grid<R>(GR_PLAIN, la(d_p7f_), geo_.T, VIS_R, VIS_R);
       launch_fft<R>(2, la(d_cols_), cells_, 2, 0);
       p9(IMG_TMP);
       launch_img_dot<R>(la(d_img_), IMG_TMP2, IMG_TMP);
-      launch_img_normalise<R>(la(d_img_), IMG_TMP2, IMG_TMP, SC_LAM0 + k);
+      const int at = first + k;                    // quotient `at` is kept in a ring
+      launch_img_normalise<R>(la(d_img_), IMG_TMP2, IMG_TMP, SC_LAM0 + at % kNormRound,
+                              at > 0 ? SC_LAM0 + (at - 1) % kNormRound : -1, rtol);
     }
     hip_check(hipGetLastError(), "power iteration launch");
     double sc[NUM_SCALARS];
     read_scalars(sc);
     for (int k = 0; k < round && !done; ++k, ++it) {
-      const double lam_new = sc[SC_LAM0 + k];
+      const double lam_new = sc[SC_LAM0 + (first + k) % kNormRound];
       done = it > 0 && std::fabs(lam_new - lam) <= rtol * std::fabs(lam_new);
       lam = lam_new;
     }
   }
+  write_scalar(SC_HALT, 0.0);
   if (iters_out) *iters_out = it;
   return lam;
 }

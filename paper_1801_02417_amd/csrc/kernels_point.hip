@@ -121,9 +121,11 @@ __global__ void __launch_bounds__(256) img_dot_kernel(const ProbDesc* __restrict
 
 // dst = src / ||src||, ||src||^2 summed from img_dot_kernel's partials by every workgroup (in the
 // order finalize_kernel sums them), and scal[scalar] their dot product: one launch instead of two
-// sums and a scaling.
+// sums and a scaling.  If that is within rtol of scal[prev] (prev < 0: no test), the problem is halted:
+// the kernels queued after this one leave at once.
 template <typename R>
-__global__ void __launch_bounds__(256) img_normalise_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int dst, int src, int scalar) {
+__global__ void __launch_bounds__(256) img_normalise_kernel(const ProbDesc* __restrict__ descs, const int4* __restrict__ items, int dst, int src, int scalar,
+                                                            int prev, double rtol) {
   __shared__ double red[8];
   const int4 it = items[blockIdx.x];
   const ProbDesc& P = descs[it.x];
@@ -134,7 +136,10 @@ __global__ void __launch_bounds__(256) img_normalise_kernel(const ProbDesc* __re
   const double nv = block_sum_partials(gen_part(P, 1), parts, red);
   if (it.y == 0) {
     const double d = block_sum_partials(gen_part(P, 0), parts, red);
-    if (threadIdx.x == 0) P.scal[scalar] = d;
+    if (threadIdx.x == 0) {
+      P.scal[scalar] = d;
+      if (prev >= 0 && fabs(d - P.scal[prev]) <= rtol * fabs(d)) P.scal[SC_HALT] = 1.0;
+    }
   }
   const R f = R(nv > 0.0 ? 1.0 / sqrt(nv) : 0.0);
   v.x *= f; v.y *= f; v.z *= f; v.w *= f;
@@ -245,8 +250,8 @@ template <typename R> void launch_npcount(const LaunchArgs& a) {
 template <typename R> void launch_img_dot(const LaunchArgs& a, int xs, int ys) {
   if (a.nitems > 0) hipLaunchKernelGGL((img_dot_kernel<R>), dim3(a.nitems), dim3(256), 0, a.stream, a.descs, a.items, xs, ys);
 }
-template <typename R> void launch_img_normalise(const LaunchArgs& a, int dst, int src, int scalar) {
-  if (a.nitems > 0) hipLaunchKernelGGL((img_normalise_kernel<R>), dim3(a.nitems), dim3(256), 0, a.stream, a.descs, a.items, dst, src, scalar);
+template <typename R> void launch_img_normalise(const LaunchArgs& a, int dst, int src, int scalar, int prev, double rtol) {
+  if (a.nitems > 0) hipLaunchKernelGGL((img_normalise_kernel<R>), dim3(a.nitems), dim3(256), 0, a.stream, a.descs, a.items, dst, src, scalar, prev, rtol);
 }
 template <typename R> void launch_fill(void* p, size_t count, hipStream_t s) {
   if (count == 0) return;
@@ -304,7 +309,7 @@ template <typename R> void launch_to_double(const void* src, double* dst, size_t
   template void launch_img_sumsq<R>(const LaunchArgs&, int, int, int);      \
   template void launch_npcount<R>(const LaunchArgs&);                       \
   template void launch_img_dot<R>(const LaunchArgs&, int, int);             \
-  template void launch_img_normalise<R>(const LaunchArgs&, int, int, int);  \
+  template void launch_img_normalise<R>(const LaunchArgs&, int, int, int, int, double); \
   template void launch_fill<R>(void*, size_t, hipStream_t);                 \
   template void launch_scale<R>(void*, size_t, double, hipStream_t);       \
   template void launch_gather_rows<R>(const double*, const int*, void*, long long, hipStream_t); \

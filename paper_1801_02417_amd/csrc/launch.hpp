@@ -66,8 +66,8 @@ template <typename R> void launch_img_sumsq(const LaunchArgs& a, int slot, int c
 template <typename R> void launch_npcount(const LaunchArgs& a);
 template <typename R> void launch_img_dot(const LaunchArgs& a, int xs, int ys);
 // dst = src / ||src|| with ||src||^2 from launch_img_dot's partials (x, src), whose dot product
-// goes to scal[scalar]
-template <typename R> void launch_img_normalise(const LaunchArgs& a, int dst, int src, int scalar);
+// goes to scal[scalar]; the problem is halted if that is within rtol of scal[prev] (prev < 0: no test)
+template <typename R> void launch_img_normalise(const LaunchArgs& a, int dst, int src, int scalar, int prev, double rtol);
 template <typename R> void launch_fill(void* p, size_t count, hipStream_t s);
 // TV priors (items: {prob, block of 256 pixels, -, partial index}): the dual step of
 // Algorithm 3 on X, Psi A into IMG_PSIA, and the prior's value of IMG_S into region 0 partials

@@ -2,6 +2,8 @@
 grow towards the largest eigenvalue of Re phi^dagger phi (from the oracle, in 64 bits) and never
 beyond it; a loose test stops at the step at which it first holds; for every tap count, with fewer
 and more rows than a round needs, FP32 and FP64 contexts (the iteration itself is always FP64)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -40,5 +42,37 @@ def test_quotients_grow_to_the_norm(taps, M, prec):
         steps = [s.opnorm(k, 0.0) for k in range(1, 12)]
         first = next(k for k in range(1, 11) if abs(steps[k] - steps[k - 1]) <= 0.05 * steps[k])
         assert s.opnorm(500, 0.05) == steps[first]
+    finally:
+        s.close()
+
+
+def _best(f, n=7):
+    best = 1e9
+    for _ in range(n):
+        t = time.perf_counter()
+        f()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+@pytest.mark.parametrize("stop", [2, 3, 5, 9])
+def test_a_loose_test_costs_the_steps_it_takes(stop):
+    """The steps queued beyond the one that meets the test must not run: the call takes the time of as
+    many steps with the test off (some 0.3 ms each here), and half as much again at most."""
+    wl = wk.ring256()
+    s = P.Solver(wl.n, wl.uv, taps=wl.taps, precision=P.PSARA_FP64)
+    try:
+        q = [s.opnorm(k, 0.0) for k in range(1, stop + 1)]
+        rtol = 1.0 if stop == 2 else abs(q[-1] / q[-2] - 1.0) * q[-2] / q[-1] * (1.0 + 1e-9)
+        assert s.opnorm(500, rtol) == q[-1]
+        fixed, loose = _best(lambda: s.opnorm(stop, 0.0)), _best(lambda: s.opnorm(500, rtol))
+        say(f"[opnorm] stop at step {stop}: {loose * 1e3:.2f} ms, {stop} steps {fixed * 1e3:.2f} ms")
+        assert loose <= 1.5 * fixed
+        s.set_prior(4, 1e-3)
+        s.set_data(np.ones((wl.M, 4), complex), 1.0)
+        s.opnorm(500, rtol)
+        s.set_steps()
+        s.solve(P.PSARA_NNLS_INIT, 3, report=False)
+        assert np.any(s.image())                          # nothing is left halted
     finally:
         s.close()
