@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "grid_cut.hpp"
+
 namespace psara {
 
 constexpr int kMaxBases = 9;     // Dirac + Db1..Db8
@@ -16,9 +18,6 @@ constexpr int kMaxFilter = 16;   // Db8 has 16 taps
 constexpr int kMaxTaps = 8;      // Kaiser-Bessel taps per dimension
 constexpr int kMaxCheb = 17;     // Chebyshev coefficients per tap (degree <= 16)
 constexpr int kMaxLevels = 8;
-constexpr int kRunMax = 32;         // longest run of same-window visibilities one lane group takes
-constexpr int kChunkEntries = 1024; // largest gridding chunk (entries per workgroup, staged in LDS)
-constexpr int kLeastChunk = 64;     // smallest chunk size
 constexpr int kGridThreads = 512;   // threads per gridding workgroup (64 lane groups of 8)
 constexpr int kSmallChunk = 16;     // a chunk of at most this many entries is gridded by one wave
 constexpr int kGridFactorItem = -1;  // gridding work item that stores the pass's factor

@@ -105,66 +105,28 @@ Geometry build_geometry(int n, int64_t M, const double* uv, int alpha, int T) {
   return g;
 }
 
-// The entries the chunks are cut for.  The default asks for the smallest size at which no tile
-// has more than kMaxTileChunks chunks and all chunks together are at most kMaxSmallChunks (two
-// workgroups per CU): a problem that does not fill the GPU is bound by its longest chunk, and the
-// column inverse FFT, which adds a tile's slots one after the other, by the tile with the most.
-// Another size is taken as asked for.
-//   us per iteration at 1024, 512, 256, 128, 64 entries (most chunks of one tile):
-//   32^2 FP64, 600 rows   46.5 46.4 46.4 42.5 39.6  (1 1 1 2 4)
-//   64^2 FP32, 1511 rows  37.6 37.6 37.6 37.3 35.1  (1 1 1 2 3)
-//   64^2 FP64, 3000 rows  70.0 67.4 56.2 55.6 60.5  (1 2 3 5 9)
-//   128^2 FP32, 12000     47.8 44.4 42.3 43.7 48.0  (1 2 3 6 11)
-//   128^2 FP32 with Mueller matrices, 20001   57.4 at 1024, 44.9 at 256 (1, 4)
-//   64^2 FP32, 30000      52.7 48.7 54.0 74.0 115.7 (5 10 20 39 77)
-//   256^2 FP32, 2e5       94.9 95.7 100  126  182   (4 8 16 31 61; 848 chunks at 1024)
-int grid_chunk_entries(const Geometry& g, int asked) {
-  constexpr int kMaxTileChunks = 4, kMaxSmallChunks = 512, kLeast = 64;
-  static_assert(kRunMax <= kLeast, "a run fits a chunk");
-  int best = asked;
-  for (int c = asked / 2; asked == kChunkEntries && c >= kLeast; c /= 2) {
-    long long most = 0, all = 0;
-    for (size_t t = 0; t < g.row_beg.size(); ++t) {
-      const long long k = (g.row_end[t] - g.row_beg[t] + c - 1) / c;
-      most = std::max(most, k);
-      all += k;
-    }
-    if (most > kMaxTileChunks || all > kMaxSmallChunks) break;
-    best = c;
-  }
-  return best;
-}
-
 void build_grid_chunks(Geometry& g, int asked) {
   const int ntg = g.ntsg * g.ntsg;
-  const int chunk_entries = grid_chunk_entries(g, asked);
+  const int chunk_entries = grid_chunk_entries(g.k0, g.row_beg, g.row_end, asked);
   g.run_pack.clear();
   g.chunks.clear(); g.chunk_ent.clear(); g.tile_slots.clear(); g.slot_box.clear(); g.tile_box.clear(); g.small_ids.clear();
   g.n_slots = 0;
   g.chunk_asked = asked;
   g.chunk_entries = chunk_entries;
-  // runs: consecutive rows of a tile with the same window start (their taps hit the
-  // same cells), split at kRunMax; chunks of whole runs with <= chunk_entries entries, runs
-  // ordered longest first inside a chunk so the lanes of a wave loop for similar lengths.
+  // chunks of whole runs, the runs ordered longest first inside a chunk so the lanes of a wave loop
+  // for similar lengths.
   // Every chunk accumulates its tile plus the T-1 halo in its own slot; the column inverse
   // FFT sums the slots of a cell's tile and of the three tiles whose halos reach it.
   for (int t = 0; t < ntg; ++t) {
-    std::vector<std::pair<int, int>> runs;
-    for (int e = g.row_beg[t]; e < g.row_end[t];) {
-      int f = e + 1;
-      while (f < g.row_end[t] && f - e < kRunMax && g.k0[f] == g.k0[e]) ++f;
-      runs.push_back({e, f - e});
-      e = f;
-    }
+    std::vector<Run> runs = tile_runs(g.k0, g.row_beg[t], g.row_end[t]);
     const int first_slot = g.n_slots;
     int u_lo1 = 255, u_hi1 = 0, u_lo2 = 255, u_hi2 = 0;   // union of the tile's boxes (empty: none)
     size_t r = 0;
     while (r < runs.size()) {
       const size_t r0 = r;
-      int entries = 0;
-      while (r < runs.size() && (entries + runs[r].second <= chunk_entries || r == r0)) entries += runs[r++].second;
+      r = chunk_end(runs, r, chunk_entries);
       std::stable_sort(runs.begin() + r0, runs.begin() + r,
-                       [](const std::pair<int, int>& x, const std::pair<int, int>& y) { return x.second > y.second; });
+                       [](const Run& x, const Run& y) { return x.second > y.second; });
       const int base = (int)g.run_pack.size();
       int lo = g.row_end[t], hi = g.row_beg[t];
       for (size_t q = r0; q < r; ++q) {
