@@ -387,19 +387,23 @@ int psara_layout(const psara_ctx* ctx, int64_t* perm);
 
 /* ---- profiling --------------------------------------------------------------------------- */
 
-/* Run `iters` iterations of Algorithm 1 in `mode` with every launch on the context stream
- * (no graph, the two independent branches serialised), bracket each pass with HIP events,
- * and write the average duration in milliseconds of each pass to ms_per_pass[0..8]:
+/* Run `iters` iterations of Algorithm 1 in `mode` with every pass as a launch of its own on the
+ * context stream (no graph, the two independent branches serialised), bracket each pass with HIP
+ * events, and write the average duration in milliseconds of each pass to ms_per_pass[0..8]:
  * [0] primal / epigraph / Dirac dual step fused with the zero-padding and row FFT (P1+P4),
  * [1] SARA analysis + dual A + synthesis (P2+P3, coarse levels fused), [2] and [3] zero (their
  * work is timed in [1] and [0]), [4] column FFT (P5), [5] de-grid + dual B (P6), [6] grid (P7),
  * [7] column inverse FFT (P8, which also sums the partial tiles of split gridding tiles),
- * [8] row inverse FFT + crop (P9), then runs `iters` more iterations in the order the captured
- * graphs use and writes to ms_per_pass[9] the average duration of the pass that fuses P9 with
- * the next iteration's P1+P4 (0 when iters < 2) and to ms_per_pass[10] that of the pass that
- * fuses P6 and P7 where the iterations of `mode` run it in place of [5] and [6] (modes with no
- * SARA branch beside the data passes: PSARA_NNLS_INIT; 0 otherwise).  ms_per_pass holds
- * 11 doubles.  The iterations really run (the state advances by 2 * iters iterations). */
+ * [8] row inverse FFT + crop (P9), then runs `iters` more iterations with the launches of the
+ * captured graphs and writes to ms_per_pass[9] the average duration of the pass that fuses P9 with
+ * the next iteration's P1+P4 (0 when iters < 2) and to ms_per_pass[10] that of the launch that
+ * the iterations of `mode` run in place of [5] and [6], where they run P6 and P7 in one: the fused
+ * pass (PSARA_NNLS_INIT; beside a SARA branch on another stream where the gridding chunks are
+ * full or few), or the fused pass with the coarse levels of [1] beside it in the same launch (sides
+ * up to 256 in FP32 and 128 in FP64, where [4] and [7] share their launches with the rest of [1],
+ * so that the sum of the passes is not an iteration's time).  0 where they run [5] and [6].
+ * ms_per_pass holds 11 doubles.  The iterations really run (the state advances by 2 * iters
+ * iterations, with the same bits as those of psara_solve). */
 psara_status psara_profile_passes(psara_ctx* ctx, psara_mode mode, int iters, double* ms_per_pass);
 
 /* Batched psara_solve_adaptive: every member stops on its own criteria (its launches then

@@ -886,9 +886,10 @@ void launch_p8(const PassLists& L, int mode, hipStream_t s) {
   launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, pm_tv(mode) ? 2 : fused_vis<R>(L, mode) ? 1 : 3, 0);
 }
 
-// The passes of one iteration between the row passes, the prior's stages beside them
+// The passes of one iteration between the row passes, the prior's stages beside them (ev: NULL, or
+// events to record before and after the launch of P6 and P7)
 template <typename R>
-void launch_paired(const PassLists& L, int mode, hipStream_t s) {
+void launch_paired(const PassLists& L, int mode, hipStream_t s, hipEvent_t* ev = nullptr) {
   auto la = [&](const DevItems& d) { return lists_la(L, d, s); };
   if (pm_tv(mode)) {
     launch_p5_tv_dual<R>(la(L.cols), la(L.img));
@@ -897,7 +898,9 @@ void launch_paired(const PassLists& L, int mode, hipStream_t s) {
     return;
   }
   launch_p5_analysis<R>(la(L.cols), la(L.ana_d[1]));
+  if (ev) hip_check(hipEventRecord(ev[0], s), "event record");
   launch_grid_coarse<R>(la(L.p7f), la(L.coarse), L.taps);
+  if (ev) hip_check(hipEventRecord(ev[1], s), "event record");
   launch_p8_synthesis<R>(la(L.cols), la(L.synfinal));
 }
 
@@ -1501,9 +1504,9 @@ void Engine<R>::set_state(const double* buf) {
 
 // Run `iters` iterations of every problem in L with every pass on stream s, bracketed by HIP
 // events, and return the average duration of each pass (P1..P9, with P6 and P7 as separate
-// passes) in milliseconds in ms[0..8]; then `iters` iterations in the captured graphs' order,
-// returning the average durations of the fused P9 + P1 + P4 pass in ms[9] and, in the modes
-// whose iterations fuse P6 and P7, of that pass in ms[10] (0 otherwise).
+// passes) in milliseconds in ms[0..8]; then `iters` iterations with the launches of the captured
+// graphs, returning the average durations of the fused P9 + P1 + P4 pass in ms[9] and, where
+// one launch runs P6 and P7, of that launch in ms[10] (0 otherwise).
 template <typename R>
 void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, double* ms) {
   constexpr int NP = 9;
@@ -1511,7 +1514,7 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
   for (int i = 0; i <= NP; ++i) hip_check(hipEventCreate(&ev[i]), "event");
   for (int i = 0; i <= NP + 1; ++i) ms[i] = 0.0;
   const bool sparse = (mode != PM_INIT) && L.sparse;
-  const bool fused = fused_vis<R>(L, mode);
+  const bool fused = fused_vis<R>(L, mode), pair = sparse && paired<R>(L, mode);
   // P5 .. P8 with P6 and P7 as two passes (where the iterations fuse them, with the same bits)
   auto p5_p8 = [&]() {
     launch_fft<R>(1, lists_la(L, L.cols, s), L.cells, 0, 0);
@@ -1523,8 +1526,13 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
     launch_fft<R>(2, lists_la(L, L.cols, s), L.cells, 3, 0);
     hip_check(hipEventRecord(ev[8], s), "event record");
   };
-  // P5 .. P8 as the iterations run them, with the fused P6 + P7 pass timed where they use it
+  // the prior's branch and P5 .. P8 as the iterations run them, one launch of P6 and P7 timed
   auto p5_p8_run = [&]() {
+    if (pair) {
+      launch_paired<R>(L, mode, s, ev + 2);
+      return;
+    }
+    if (sparse) launch_sara_dual<R>(L, s);
     launch_fft<R>(1, lists_la(L, L.cols, s), L.cells, 0, 0);
     hip_check(hipEventRecord(ev[2], s), "event record");
     launch_p6_p7<R>(L, mode, s);
@@ -1552,7 +1560,6 @@ void profile_iterations(const PassLists& L, int mode, int iters, hipStream_t s, 
   // the pass fusing P9 with the next P1+P4, timed inside a chain of iterations in graph order
   if (iters > 0) launch_primal_fft<R>(mode, lists_la(L, L.rows, s), L.rcells);
   for (int k = 0; k < iters; ++k) {
-    if (sparse) launch_sara_dual<R>(L, s);
     p5_p8_run();
     float t = 0.f;
     if (k + 1 < iters) {

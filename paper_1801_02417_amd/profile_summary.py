@@ -34,11 +34,11 @@ PASS_KERNELS = {
     0: ("void psara::fft_pass_kernel<float, 512, 0, 0>", "fft_pass.hpp"),
     4: ("void psara::fft_pass_kernel<float, 512, 1, -1>", "fft_pass.hpp"),
     5: ("void psara::degrid_kernel<float, 0, 8>", "vis.hpp"),
-    6: ("void psara::grid_kernel<float, 1, 8>", "vis.hpp"),
+    6: ("void psara::grid_kernel<float, 0, 8>", "vis.hpp"),
     7: ("void psara::fft_pass_kernel<float, 512, 2, -1>", "fft_pass.hpp"),
     8: ("void psara::fft_pass_kernel<float, 512, 3, -1>", "fft_pass.hpp"),
     9: ("void psara::fft_pass_kernel<float, 512, 4, 0>", "fft_pass.hpp"),
-    10: ("void psara::degrid_grid_kernel<float, 0, 8>", "vis.hpp"),
+    10: ("void psara::grid_coarse_kernel<float, 8>", "vis.hpp+dwt.hpp"),
 }
 
 
@@ -91,10 +91,13 @@ def traffic(a) -> None:
     for pid, (prefix, src) in PASS_KERNELS.items():
         fb = _counter(fetch, prefix, "FETCH_SIZE") * 1024.0 * f_scale
         wb = _counter(write, prefix, "WRITE_SIZE") * 1024.0 * w_scale
-        with open(os.path.join(HERE, "csrc", src), "rb") as fh:
-            sha = hashlib.sha256(fh.read()).hexdigest()
+        sha = hashlib.sha256()
+        for part in src.split("+"):
+            with open(os.path.join(HERE, "csrc", part), "rb") as fh:
+                sha.update(fh.read())
         out["passes"][str(pid)] = {"kernel": prefix, "fetch_bytes": round(fb), "write_bytes": round(wb),
-                                   "hbm_bytes_per_launch": round(fb + wb), "source": src, "source_sha256": sha}
+                                   "hbm_bytes_per_launch": round(fb + wb), "source": src,
+                                   "source_sha256": sha.hexdigest()}
     with open(a.out, "w") as fh:
         json.dump(out, fh, indent=1)
     print(json.dumps(out, indent=1))

@@ -502,7 +502,7 @@ PASS_NAMES = ("P1+P4 primal/epigraph/Dirac dual + zero-pad + row FFT", "P2+P3 SA
               "(in P2+P3)", "(in P1+P4)", "P5 column FFT", "P6 de-grid + dual B", "P7 grid",
               "P8 column inverse FFT (+ split-tile sums)", "P9 row inverse FFT + crop",
               "P9+P1+P4 fused (row inverse FFT, primal step, row FFT)",
-              "P6+P7 fused (de-grid + dual B + grid)")
+              "P6+P7 in one launch (with the coarse SARA levels where the iterations pair them)")
 N_PASSES = len(PASS_NAMES)
 
 
