@@ -270,8 +270,9 @@ psara_status psara_set_gamma(psara_ctx* ctx, double gamma);
  * summation order of the gridding and of the de-gridding norm (results differ at rounding level,
  * never in what is computed); every solve starts with the defaults. */
 typedef struct {
-    int grid_chunk;      /* gridding entries per workgroup: 256, 512 or 1024 (default 1024, which
-                            a problem too small to fill the GPU cuts down to 64 or more) */
+    int grid_chunk;      /* gridding entries per workgroup: 256 or 512, or 1024 (the default) for as
+                            many as suit the problem: 1024, and down to 64 where that leaves the
+                            GPU unfilled */
     int degrid_item;     /* visibilities per de-gridding workgroup: a power of two in [64, 1024]
                             (default 256) */
     int analysis_wide;   /* bit 0: 16-wide output tiles for the analysis bands of side >= 128 of
@@ -296,8 +297,9 @@ enum {
 
 /* The autotuner: times the iteration of `mode` (chains of 8 captured iterations, best of three)
  * under candidate shapes, one parameter at a time from the current ones (grid_chunk 1024 / 512 /
- * 256, degrid_item 256 / 128 / 512, analysis_wide 1 / 0 / 3 / 2, fft_cells default / 1024 / 2048), keeps
- * a candidate that beats the incumbent by 1 %, and applies the fastest.  The iteration state is
+ * 256, degrid_item 256 / 128 / 512, analysis_wide 1 / 0 / 3 / 2, fft_cells default / 1024 / 2048; not
+ * the grid_chunk that the default is cut to, nor degrid_item where the iterations run P6 and P7 in
+ * one launch), keeps a candidate that beats the incumbent by 1 %, and applies the fastest.  The iteration state is
  * saved and restored around the trials (the stored state exactly; the operator images the next
  * primal step reads are recomputed).  A shape class is the precision, taps, image side, levels,
  * basis mask and the visibility count's power of two.  flags: PSARA_TUNE_USE_CACHE,

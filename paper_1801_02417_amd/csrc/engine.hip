@@ -1590,6 +1590,11 @@ void Engine<R>::profile(int mode, int iters, double* ms) {
   profile_iterations<R>(pl_, mode, iters, s0_, ms);
 }
 
+template <typename R>
+bool Engine<R>::degrids(int mode) const { return !fused_vis<R>(pl_, mode); }
+template <typename R>
+bool Batch<R>::degrids(int mode) const { return !fused_vis<R>(pl_, mode); }
+
 template struct Engine<float>;
 template struct Engine<double>;
 

@@ -163,6 +163,7 @@ struct Engine {
   void profile(int mode, int iters, double* ms);
   size_t coef_elems() const { return coef_elems_; }
   const Tuning& tuning() const { return tuning_; }
+  bool degrids(int mode) const;        // whether the iterations of `mode` launch P6 as a pass of its own
   int fft_cells() const { return cells_; }
   // new launch shapes: the gridding lists are cut again, the work lists rebuilt, the partial
   // sums and slots reallocated and the graphs dropped; the iteration state is kept
@@ -265,6 +266,7 @@ struct Batch {
   // (no work launched), and queue `chunks` chunks (the members' criteria set by stop_begin)
   void capture_adaptive(int mode, int check_every);
   void launch_adaptive(int mode, int chunks, int check_every);
+  bool degrids(int mode) const;        // as Engine's
   hipStream_t stream() const { return s0_; }
   int size() const { return (int)members_.size(); }
 

@@ -128,10 +128,15 @@ double time_runs(F&& run, hipStream_t stream, int iters) {
 }
 
 // Coordinate search over the four parameters from `start`, each candidate timed by `measure`
-// (which applies it); a candidate must beat the incumbent by 1 % to replace it.  Returns the
-// choice and writes the time of `start` and of the choice.
-template <class M>
-Tuning search(const Tuning& start, int K, bool fp32, M&& measure, double* t_start, double* t_best) {
+// (which applies it); a candidate must beat the incumbent by 1 % to replace it.  Candidates that
+// would launch the same work as the incumbent are left out, as only noise could choose them: chunk
+// sizes that the incumbent's is cut to already (`chunk_in_use`, 0 if the problems differ), and
+// the de-gridding item where the incumbent's iterations launch no de-gridding of its own
+// (`degrids`).  Both are asked with the incumbent applied.  Returns the choice and writes the time
+// of `start` and of the choice.
+template <class M, class C, class D>
+Tuning search(const Tuning& start, int K, bool fp32, M&& measure, C&& chunk_in_use, D&& degrids, double* t_start,
+              double* t_best) {
   Tuning best = start;
   double tb = measure(best);
   *t_start = tb;
@@ -147,10 +152,13 @@ Tuning search(const Tuning& start, int K, bool fp32, M&& measure, double* t_star
       best = cand;
     }
   };
+  const int in_use = chunk_in_use();
   for (int v : {1024, 512, 256})
-    if (v != best.grid_chunk) { Tuning c = best; c.grid_chunk = v; consider(c); }
-  for (int v : {256, 128, 512})
-    if (v != best.degrid_item) { Tuning c = best; c.degrid_item = v; consider(c); }
+    if (v != best.grid_chunk && v != in_use) { Tuning c = best; c.grid_chunk = v; consider(c); }
+  measure(best);        // applied again for the question
+  if (degrids())
+    for (int v : {256, 128, 512})
+      if (v != best.degrid_item) { Tuning c = best; c.degrid_item = v; consider(c); }
   // (FP64 analysis tiles are 8 wide either way, so there only the all-bases bit is a candidate)
   for (int v : {1, 0, 3, 2})
     if (v != best.ana_wide && (fp32 || v == (best.ana_wide ^ psara::kAnaAllBases))) {
@@ -184,7 +192,8 @@ Tuning tune_one(psara_ctx* c, int pm, double* t0, double* t1) {
       e->set_tuning(t);
       return time_runs([&] { e->run(pm, kTrialIters); }, e->stream(), kTrialIters);
     };
-    best = search(e->tuning(), c->geo.K, std::is_same<R, float>::value, measure, t0, t1);
+    best = search(e->tuning(), c->geo.K, std::is_same<R, float>::value, measure,
+                  [&] { return e->geometry().chunk_entries; }, [&] { return e->degrids(pm); }, t0, t1);
   } catch (...) {
     e->set_state(keep.data());
     throw;
@@ -214,7 +223,12 @@ Tuning tune_batch(psara_ctx* const* ctxs, int count, int pm, double* t0, double*
       Batch<R> b(m, ctxs[0]->stream);
       return time_runs([&] { b.run(pm, kTrialIters); }, b.stream(), kTrialIters);
     };
-    best = search(m[0]->tuning(), Kmax, std::is_same<R, float>::value, measure, t0, t1);
+    best = search(m[0]->tuning(), Kmax, std::is_same<R, float>::value, measure,
+                  [&] {
+                    const int c = m[0]->geometry().chunk_entries;
+                    return std::all_of(m.begin(), m.end(), [&](Engine<R>* e) { return e->geometry().chunk_entries == c; }) ? c : 0;
+                  },
+                  [&] { return Batch<R>(m, ctxs[0]->stream).degrids(pm); }, t0, t1);
   } catch (...) {
     restore();
     throw;

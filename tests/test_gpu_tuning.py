@@ -203,3 +203,25 @@ def test_tuning_store_and_cache():
     finally:
         s.close()
         s2.close()
+
+
+@pytest.mark.parametrize("n,M,prec", [(64, 1511, "fp32"), (32, 600, "fp64"), (128, 12000, "fp32")])
+def test_autotune_leaves_alone_what_the_iterations_do_not_launch(n, M, prec):
+    """Paired iterations launch no de-gridding pass of its own, so its item size is not for noise to
+    choose; over several searches it stays the default."""
+    wl = wk.tiny(n=n, M=M, taps=8, levels=3, seed=3)
+    s = solver_for(wl, n, 8, prec, levels=3, gamma=1e-3)
+    try:
+        rng = np.random.default_rng(4)
+        Y = rng.standard_normal((M, 4)) + 1j * rng.standard_normal((M, 4))
+        s.set_data(Y, 0.3 * float(np.linalg.norm(Y)))
+        s.opnorm(30, 1e-2)
+        s.set_steps(*P.psara_step_sizes(0, 1.3 * s.phi_norm_sq))
+        for _ in range(4):
+            chosen, ms = s.autotune(P.PSARA_CONSTRAINED)
+            say(f"[autotune] n={n} {prec}: {chosen}")
+            if chosen["fft_cells"] in (0, 512):
+                assert chosen["degrid_item"] == P.DEFAULT_TUNING["degrid_item"]
+            s.set_tuning(None)
+    finally:
+        s.close()
