@@ -511,8 +511,9 @@ __device__ __forceinline__ void synthesis_final_item(const ProbDesc& P, const in
 // FP32 holds 128 x 128 elements (66 KB, which the fused gridding launch it runs beside takes
 // anyway), so that a 256^2 image needs one analysis launch before it, not two, and its branch
 // fits the data branch's launches: 94.3 -> 84.8 us per iteration at 256^2 / 2e5 rows.  Bound by
-// one CU's work on a channel of 128^2: at 16 taps 5.6 us of loads, 11 of analysis, 8.6 of
-// updates, 10 of synthesis and 2 of stores; more loads in flight, filters that take the next
+// one CU's work on a channel of 128^2: at 16 taps 5.9 us of loads, 12.7 of analysis, 8.6 of
+// updates, 9.6 of synthesis and 3.4 of stores, 40 in all (a launch of them alone takes 42), and beside
+// the fused pass 45 (7.5, 16.0, 9.3, 9.2 and 3.3); more loads in flight, filters that take the next
 // line's elements a step ahead and lanes spread over two lines for the banks gave nothing.
 // Larger images keep 64 x 64 (their branch runs beside the data branch's on another stream,
 // where a workgroup that long would be the longer one).

@@ -681,7 +681,10 @@ __device__ inline void grid_small(const ProbDesc& P, const int4 it, int src_slot
 // The same chunk by a whole workgroup of the fused pass, which has staged the entries' offsets (sf)
 // and channels (su) and, at st, their window starts relative to the tile (o1 | o2 << 8): a thread
 // owns a cell of the box or two, and finds the taps in LDS (sw: 16 per entry, k1 then k2).  Each
-// cell gets the sum that grid_small gives it.  No zeroing of the fixed-point tile, no atomics.
+// cell gets the sum that grid_small gives it.  No zeroing of the fixed-point tile, no atomics; it
+// takes the time of the fixed-point sums (64^2 31.9 us per iteration with either, 256^2 / 2e5 84.5
+// against 85.4, 32^2 FP64 37.9 against 37.4), and the sums in 64 bits, here and in grid_small, would
+// cost batches 2 to 5 % for the same error of the image.
 template <typename R, int T>
 __device__ inline void grid_small_wg(const ProbDesc& P, const int4 ch, int ne, const V2<R>* sf, const V4<R>* su,
                                      const int* st, R* sw, int box) {
@@ -815,9 +818,9 @@ __device__ __forceinline__ void grid_item(const ProbDesc& P, const int4 it, int 
 // One thread per row leaves most of the workgroup idle in a chunk of few rows, and the row's T x T
 // taps a chain of their own: there a group of eight lanes shares a row, a tap row to a lane, as
 // long as one pass of the groups covers the chunk.  us per iteration, a thread to a row -> this:
-// 64^2 34.4 -> 33.0, initialisation of 256^2 / 2e5 65.5 -> 64.0 and of 512^2 / 1e6 206 -> 200, TV at
-// 256^2 65.2 -> 63.7; with two passes (128 rows) 128^2 with Mueller matrices lost 1.5 %.  Not in
-// FP64, where the lanes' polynomials cost registers that spill (32^2 39.0 -> 41.1).
+// 64^2 32.8 -> 31.9, its initialisation 29.7 -> 28.4 and that of 512^2 / 1e6 193 -> 184 (256^2 / 2e5,
+// whose chunks are mostly larger: 61.9 -> 62.4); with two passes (128 rows) 128^2 with Mueller matrices
+// lost 1.5 %.  Not in FP64, where the lanes' polynomials cost registers that spill (32^2 39.0 -> 41.1).
 template <typename R, int MODE, int T>
 __device__ __forceinline__ void degrid_grid_item(const ProbDesc& P, const int4 it, int src_slot, int out_slot, int ce,
                                                  unsigned long long* acc, unsigned char* stage_raw, double* red) {
