@@ -185,7 +185,7 @@ static bool chunk_norm(int K, int levels, int c_level) { return K <= 512 && (lev
 // Whether the first analysis level of problems of sides up to n is paired under this tiling.  Not the
 // items that run every basis over a tile where there are few large ones (16-wide tiles, FP64): they
 // hold up P5, and are better off on another stream (us per iteration, paired / apart: 256^2 / 2e5 rows
-// 113 / 103, 128^2 FP64 75 / 70; with 8-wide tiles 93 / 97 at 256^2, 51 / 59 at 128^2).
+// 113 / 104, 128^2 FP64 75 / 69; with 8-wide tiles 93 / 97 at 256^2, 51 / 59 at 128^2).
 template <typename R>
 static bool pair_tiles(int n, int ana_wide) {
   return !(ana_wide & kAnaAllBases) || (sizeof(R) == 4 && dwt_ana_tile<R>(n >> 1, (ana_wide & kAnaWide) != 0) <= 8);
@@ -831,14 +831,14 @@ void launch_sara_dual(const PassLists& L, hipStream_t s) {
 // launch of more than kMaxPaired gridding chunks (a large batch, or very many rows) fills the GPU from
 // either branch, and the two share it better on their own streams; FP64 has one gridding
 // workgroup to a CU, FP32 up to four.
-//   us per iteration, chunks: paired / apart
-//   FP32  128^2, 1.2e4 rows  720: 68 / 75   1440: 112 / 114  2160: 159 / 154  2880: 209 / 195
-//         256^2, 2e5         848: 85 / 93   1696: 132 / 137  2544: 185 / 182  3392: 250 / 238
-//         64^2, 1511         816: 73 / 77   1632: 125 / 122  3264: 238 / 208
-//         128^2, 4e4         932: 80 / 90   1864: 132 / 143  3728: 256 / 244
-//   FP64  128^2, 1.2e4       180: 65 / 71   360: 83 / 80     720: 132 / 120   1440: 241 / 193
-//         32^2, 600          152: 51 / 55   304: 69 / 66     608: 105 / 93
-//         64^2, 3000         184: 67 / 74   368: 90 / 90     736: 158 / 137
+//   us per iteration of a batch, chunks: paired / apart (the faster route of P6 and P7)
+//   FP32  128^2, 1.2e4 rows  720: 65 / 73   1440: 109 / 106  2160: 154 / 148  2880: 201 / 189
+//         256^2, 2e5         1696: 128 / 134  2544: 178 / 175  3392: 241 / 231  6784: 491 / 447
+//         64^2, 1511         816: 71 / 76   1632: 119 / 118  3264: 224 / 203
+//         128^2, 4e4         932: 77 / 88   1864: 129 / 135  3728: 243 / 238
+//   FP64  128^2, 1.2e4       360: 81 / 79   540: 107 / 101   720: 130 / 117   1440: 236 / 202
+//         32^2, 600          152: 49 / 52   304: 66 / 66     608: 102 / 91
+//         64^2, 3000         184: 65 / 69   368: 88 / 86     736: 154 / 133
 template <typename R> constexpr int kMaxPaired = sizeof(R) == 4 ? 2048 : 256;
 template <typename R>
 bool paired(const PassLists& L, int mode) {
@@ -853,11 +853,11 @@ bool paired(const PassLists& L, int mode) {
 // where the chunks hold kFullChunk rows on average, since the fused pass stages and clears a
 // chunk's region whatever it holds.
 //   us per iteration beside a SARA branch, rows in a chunk: two passes / fused
-//   FP32  66: 371 / 397   172: 467 / 484   236: 249 / 238   367: 331 / 328   998: 599 / 571
-//   FP64  66: 798 / 902   172: 526 / 542   367: 407 / 377   400: 465 / 443   944: 766 / 584
-// Also with kFewChunks chunks or fewer (a launch that only its FFT cells keep from being paired): they
-// leave CUs idle, and one launch takes less than two.  1024 or 2048 cells, chunks: FP32 51: 58 / 52, 180:
-// 55 / 58; FP64 180: 82 / 72.
+//   FP32  66: 359 / 383   143: 189 / 189   172: 453 / 466   236: 240 / 231   367: 322 / 319   998: 596 / 561
+//   FP64  66: 755 / 852   172: 515 / 526   367: 403 / 367   400: 456 / 426   944: 753 / 566
+// Also with kFewChunks chunks or fewer (a launch that only its shapes keep from being paired): they
+// leave CUs idle, and one launch takes less than two.  1024 or 2048 cells, chunks: FP32 51: 48 / 46 and
+// 58 / 51, 180: 55 / 57 and 66 / 63; FP64 180: 83 / 71.
 constexpr long long kFullChunk = 200;
 template <typename R> constexpr int kFewChunks = sizeof(R) == 4 ? 128 : 256;
 template <typename R>
